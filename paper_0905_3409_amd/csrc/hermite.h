@@ -290,24 +290,27 @@ __device__ __forceinline__ void gather2d(const Geom &g, Rsrc rphi, Rsrc rgx, Rsr
 }
 
 // 3D alpha: 0 phi, 1 psi_x, 2 psi_y, 3 phi_xy, 4 psi_z, 5 phi_xz, 6 phi_yz,
-// 7 phi_xyz, with phi_xy = D_x psi_y, phi_xz = D_x psi_z, phi_yz = D_y psi_z,
-// phi_xyz = D_x D_y psi_z.
+// 7 phi_xyz, for the rules whose cross derivatives come from the cell's own
+// vertices: cell-based (B), or all zero. (tricubic_central evaluates central
+// differencing, (A), without forming them.)
 template <typename T, int MIX>
 __device__ __forceinline__ void gather3d(const Geom &g, Rsrc rphi, Rsrc rgx, Rsrc rgy, Rsrc rgz,
                                          int c0, int c1, int c2, T d[8][8])
 {
-    if constexpr (MIX == GALS_MIXED_CELL) {
-        // the 8 vertices' phi and gradients; cross derivatives per facet
-        const unsigned P = unsigned(g.pitch), S = unsigned(g.pitch) * unsigned(g.n[1]);
+    static_assert(MIX != GALS_MIXED_CENTRAL, "see tricubic_central");
+    const unsigned P = unsigned(g.pitch), S = unsigned(g.pitch) * unsigned(g.n[1]);
 #pragma unroll
-        for (int v = 0; v < 8; v++) {
-            const unsigned o = unsigned(c2 + (v >> 2)) * S + unsigned(c1 + ((v >> 1) & 1)) * P +
-                               unsigned(c0 + (v & 1));
-            d[v][0] = bload(rphi, o, T());
-            d[v][1] = bload(rgx, o, T());
-            d[v][2] = bload(rgy, o, T());
-            d[v][4] = bload(rgz, o, T());
-        }
+    for (int v = 0; v < 8; v++) {
+        const unsigned o = unsigned(c2 + (v >> 2)) * S + unsigned(c1 + ((v >> 1) & 1)) * P +
+                           unsigned(c0 + (v & 1));
+        d[v][0] = bload(rphi, o, T());
+        d[v][1] = bload(rgx, o, T());
+        d[v][2] = bload(rgy, o, T());
+        d[v][4] = bload(rgz, o, T());
+        d[v][3] = d[v][5] = d[v][6] = d[v][7] = T(0);
+    }
+    if constexpr (MIX == GALS_MIXED_CELL) {
+        // cross derivatives per facet
         const T ih[3] = {geo_ih<T>(g, 0), geo_ih<T>(g, 1), geo_ih<T>(g, 2)};
         // (a, b) = (x, y), (x, z), (y, z) into alpha 3, 5, 6; facet level along
         // the third axis c
@@ -338,72 +341,6 @@ __device__ __forceinline__ void gather3d(const Geom &g, Rsrc rphi, Rsrc rgx, Rsr
             const T xyz = (d[b + 3][4] - d[b + 2][4] - d[b + 1][4] + d[b][4]) * (ih[0] * ih[1]);
 #pragma unroll
             for (int k = 0; k < 4; k++) d[b + k][7] = xyz;
-        }
-        return;
-    }
-    const unsigned P = unsigned(g.pitch), S = unsigned(g.pitch) * unsigned(g.n[1]);
-    const unsigned xs[4] = {unsigned(c0 > 0 ? c0 - 1 : 0), unsigned(c0), unsigned(c0 + 1),
-                            unsigned(c0 + 2 <= g.nc[0] ? c0 + 2 : g.nc[0])};
-    const unsigned ys[4] = {unsigned(c1 > 0 ? c1 - 1 : 0), unsigned(c1), unsigned(c1 + 1),
-                            unsigned(c1 + 2 <= g.nc[1] ? c1 + 2 : g.nc[1])};
-    const bool xlo = c0 == 0, xhi = c0 + 1 == g.nc[0];
-    const bool ylo = c1 == 0, yhi = c1 + 1 == g.nc[1];
-    const T i2hx = geo_i2h<T>(g, 0), i2hy = geo_i2h<T>(g, 1);
-#pragma unroll
-    for (int vz = 0; vz < 2; vz++) {
-        const unsigned zo = unsigned(c2 + vz) * S;
-#pragma unroll
-        for (int vy = 0; vy < 2; vy++) {
-            const unsigned ro = zo + ys[1 + vy] * P;
-#pragma unroll
-            for (int vx = 0; vx < 2; vx++) {
-                const int v = vx + 2 * vy + 4 * vz;
-                d[v][0] = bload(rphi, ro + xs[1 + vx], T());
-                d[v][1] = bload(rgx, ro + xs[1 + vx], T());
-            }
-            if constexpr (MIX == GALS_MIXED_CENTRAL) {
-                const T u[4] = {bload(rgy, ro + xs[0], T()), bload(rgy, ro + xs[1], T()),
-                                bload(rgy, ro + xs[2], T()), bload(rgy, ro + xs[3], T())};
-                d[2 * vy + 4 * vz][2] = u[1];
-                d[1 + 2 * vy + 4 * vz][2] = u[2];
-                diff_pair(u, xlo, xhi, i2hx, d[2 * vy + 4 * vz][3], d[1 + 2 * vy + 4 * vz][3]);
-            } else {
-                d[2 * vy + 4 * vz][2] = bload(rgy, ro + xs[1], T());
-                d[1 + 2 * vy + 4 * vz][2] = bload(rgy, ro + xs[2], T());
-                d[2 * vy + 4 * vz][3] = d[1 + 2 * vy + 4 * vz][3] = T(0);
-            }
-        }
-        if constexpr (MIX == GALS_MIXED_CENTRAL) {
-            T w[4][4];  // psi_z at (ys[jy], xs[jx])
-#pragma unroll
-            for (int jy = 0; jy < 4; jy++)
-#pragma unroll
-                for (int jx = 0; jx < 4; jx++) w[jy][jx] = bload(rgz, zo + ys[jy] * P + xs[jx], T());
-            T dy[2][4];  // D_y psi_z at rows c1, c1+1 for each x sample
-#pragma unroll
-            for (int jx = 0; jx < 4; jx++) {
-                const T col[4] = {w[0][jx], w[1][jx], w[2][jx], w[3][jx]};
-                diff_pair(col, ylo, yhi, i2hy, dy[0][jx], dy[1][jx]);
-            }
-#pragma unroll
-            for (int vy = 0; vy < 2; vy++) {
-                const int b = 2 * vy + 4 * vz;
-                d[b][4] = w[1 + vy][1];
-                d[b + 1][4] = w[1 + vy][2];
-                diff_pair(w[1 + vy], xlo, xhi, i2hx, d[b][5], d[b + 1][5]);  // phi_xz
-                d[b][6] = dy[vy][1];                                       // phi_yz
-                d[b + 1][6] = dy[vy][2];
-                diff_pair(dy[vy], xlo, xhi, i2hx, d[b][7], d[b + 1][7]);    // phi_xyz
-            }
-        } else {
-#pragma unroll
-            for (int vy = 0; vy < 2; vy++) {
-                const int b = 2 * vy + 4 * vz;
-                const unsigned ro = zo + ys[1 + vy] * P;
-                d[b][4] = bload(rgz, ro + xs[1], T());
-                d[b + 1][4] = bload(rgz, ro + xs[2], T());
-                d[b][5] = d[b + 1][5] = d[b][6] = d[b + 1][6] = d[b][7] = d[b + 1][7] = T(0);
-            }
         }
     }
 }
@@ -590,6 +527,220 @@ __device__ __forceinline__ void hermite3d_full(const T d[8][8], const Basis<T> &
     Hs[0] = hxx; Hs[1] = hxy; Hs[2] = hxz;
     Hs[3] = hxy; Hs[4] = hyy; Hs[5] = hyz;
     Hs[6] = hxz; Hs[7] = hyz; Hs[8] = hzz;
+}
+
+// ---------------------------------------------------------------------------
+// The tricubic with central cross derivatives (A), without forming them. The
+// phi_xy, phi_xz, phi_yz and phi_xyz data are differences of psi_y and psi_z
+// along x and y, and the interpolant is linear in them, so along such an axis
+// the Hermite weights of a sample and of its difference combine into four
+// weights on the nodes c - 1 .. c + 2 (with u the samples and D their
+// difference: w0 u_c + w1 u_c+1 + w2 D_c + w3 D_c+1). psi_z is then a 4 x 4
+// stencil times the two z data weights, psi_y a 4 x 2 stencil, and the
+// one-sided differences of the grid's first and last cell change the weights
+// of one axis instead of 20 difference pairs per node. Contracted x, y, z:
+// 192 multiply-adds, the differences with their one-sided forms and selects
+// (240 instructions a node) gone. phi enters as its differences from the
+// cell's first vertex: its derivatives are divided differences, and rounding
+// then acts on values of the size of h |grad phi| instead of |phi|.
+//
+// Bound: vector issue (FP64 and the vector potential), the L1's rate for 64
+// scattered loads a node where the trace is cheap. Measured against forming
+// the cross derivatives, us per step on one box: 257^3 FP32 vector potential
+// 610 -> 540, 101^3 FP64 deformation field 53 -> 43, 141 x 131 x 121 FP64
+// vector potential 250 -> 185, 385^3 FP32 rotation 980 -> 935; 10^6 points in
+// FP32 363 -> 334 (with their transposed copy). Loads grouped by x node instead of by row cost the rotation 15 %
+// and the points 75 % (a row's loads no longer meet in the L1); two or three
+// groups in flight measured no faster than one and took the FP64 kernels from
+// three waves per SIMD to two.
+// ---------------------------------------------------------------------------
+template <typename T>
+struct StencilWeights {
+    T w[4], dw[4], ddw[4];
+};
+
+// Weights over the nodes c - 1 .. c + 2 from the Hermite weights a (w0, w1,
+// w2, w3) of one derivative order; i2h = 1 / (2 h). At the first (last) cell
+// the node c - 1 (c + 2) does not exist and gets weight 0.
+template <typename T>
+__device__ __forceinline__ void stencil_weights(const T *a, T i2h, bool lo, bool hi, T *w)
+{
+    const T p = a[2] * i2h, q = a[3] * i2h;
+    w[0] = -p;
+    w[1] = a[0] - q;
+    w[2] = a[1] + p;
+    w[3] = q;
+    if (__builtin_expect(lo, 0)) {  // D_c one-sided: (4 u_c+1 - 3 u_c - u_c+2) / 2h
+        w[0] = T(0);
+        w[1] = a[0] - (T(3) * p + q);
+        w[2] = a[1] + T(4) * p;
+        w[3] = q - p;
+    }
+    if (__builtin_expect(hi, 0)) {  // D_c+1 one-sided: (3 u_c+1 - 4 u_c + u_c-1) / 2h
+        w[0] = q - p;
+        w[1] = a[0] - T(4) * q;
+        w[2] = a[1] + (p + T(3) * q);
+        w[3] = T(0);
+    }
+}
+
+// Value, gradient G and (SECOND) Hessian Hs (row-major 3 x 3).
+template <typename T, bool SECOND>
+__device__ __forceinline__ void tricubic_central(const Geom &g, Rsrc rphi, Rsrc rgx, Rsrc rgy,
+                                                 Rsrc rgz, const int *c, const T *xi, T &H, T *G,
+                                                 T *Hs)
+{
+    Basis<T> bx, by, bz;
+    StencilWeights<T> sx, sy;  // x and y weights of psi_y and psi_z
+    basis<T, SECOND>(xi[0], geo_h<T>(g, 0), geo_ih<T>(g, 0), bx);
+    basis<T, SECOND>(xi[1], geo_h<T>(g, 1), geo_ih<T>(g, 1), by);
+    basis<T, SECOND>(xi[2], geo_h<T>(g, 2), geo_ih<T>(g, 2), bz);
+    const bool xlo = c[0] == 0, xhi = c[0] + 1 == g.nc[0];
+    const bool ylo = c[1] == 0, yhi = c[1] + 1 == g.nc[1];
+    const T i2hx = geo_i2h<T>(g, 0), i2hy = geo_i2h<T>(g, 1);
+    stencil_weights(bx.w, i2hx, xlo, xhi, sx.w);
+    stencil_weights(bx.dw, i2hx, xlo, xhi, sx.dw);
+    stencil_weights(by.w, i2hy, ylo, yhi, sy.w);
+    stencil_weights(by.dw, i2hy, ylo, yhi, sy.dw);
+    if constexpr (SECOND) {
+        stencil_weights(bx.ddw, i2hx, xlo, xhi, sx.ddw);
+        stencil_weights(by.ddw, i2hy, ylo, yhi, sy.ddw);
+    }
+    // byte offsets are formed by bload; a node outside the grid repeats its
+    // neighbour (its weight is 0), so padding is never read
+    const unsigned P = unsigned(g.pitch), S = unsigned(g.pitch) * unsigned(g.n[1]);
+    const unsigned o0 = unsigned(c[2]) * S + unsigned(c[1]) * P + unsigned(c[0]);
+    const unsigned xm = xlo ? 0u : 1u, xp = xhi ? 0u : 1u;  // steps to c - 1 and from c + 1
+    const unsigned ym = ylo ? 0u : P, yp = yhi ? 0u : P;
+    const unsigned row[4] = {o0 - ym, o0, o0 + P, o0 + P + yp};
+
+    // Eight groups of eight samples, four per plane c2 + vz: psi_z on rows
+    // c1 - 1 and c1, on rows c1 + 1 and c1 + 2, then psi_y, phi and psi_x on
+    // row c1 and on row c1 + 1. Whole rows at a time keep a row's loads in the
+    // cache lines they share.
+    auto load = [&](int q, T *u) {
+        const unsigned zo = q < 4 ? 0u : S;
+        const int part = q & 3;
+        if (part < 2) {
+#pragma unroll
+            for (int r = 0; r < 2; r++) {
+                const unsigned o = row[2 * part + r] + zo;
+                u[4 * r] = bload(rgz, o - xm, T());
+                u[4 * r + 1] = bload(rgz, o, T());
+                u[4 * r + 2] = bload(rgz, o + 1u, T());
+                u[4 * r + 3] = bload(rgz, o + 1u + xp, T());
+            }
+        } else {
+            const unsigned o = row[part - 1] + zo;
+            u[0] = bload(rgy, o - xm, T());
+            u[1] = bload(rgy, o, T());
+            u[2] = bload(rgy, o + 1u, T());
+            u[3] = bload(rgy, o + 1u + xp, T());
+            u[4] = bload(rphi, o, T());
+            u[5] = bload(rphi, o + 1u, T());
+            u[6] = bload(rgx, o, T());
+            u[7] = bload(rgx, o + 1u, T());
+        }
+    };
+    // a[dx dy]: sums over x and y of one plane's samples, derivative orders dx
+    // and dy, those with phi-like z weights (0) and psi_z (1)
+    struct Acc {
+        T a00, a10, a01, a20, a11, a02;
+    };
+    Acc A[2] = {};
+    T ref = T(0);
+    auto dot = [](const T *u, const T *w) { return u[0] * w[0] + u[1] * w[1] + u[2] * w[2] + u[3] * w[3]; };
+    auto sums = [&](Acc &a, bool first, T x0, T x1, T x2, T wy, T dwy, T ddwy) {
+        a.a00 = first ? x0 * wy : a.a00 + x0 * wy;
+        a.a01 = first ? x0 * dwy : a.a01 + x0 * dwy;
+        a.a10 = first ? x1 * wy : a.a10 + x1 * wy;
+        if constexpr (SECOND) {
+            a.a02 = first ? x0 * ddwy : a.a02 + x0 * ddwy;
+            a.a11 = first ? x1 * dwy : a.a11 + x1 * dwy;
+            a.a20 = first ? x2 * wy : a.a20 + x2 * wy;
+        }
+    };
+    auto add = [&](Acc &a, bool first, const T *u, T wy, T dwy, T ddwy) {
+        sums(a, first, dot(u, sx.w), dot(u, sx.dw), SECOND ? dot(u, sx.ddw) : T(0), wy, dwy, ddwy);
+    };
+    auto sum = [&](int q, const T *u) {
+        const int part = q & 3;
+        if (part < 2) {
+#pragma unroll
+            for (int r = 0; r < 2; r++) {
+                const int jy = 2 * part + r;
+                add(A[1], jy == 0, u + 4 * r, sy.w[jy], sy.dw[jy], SECOND ? sy.ddw[jy] : T(0));
+            }
+        } else {
+            const int vy = part - 2;
+            if (q == 2) ref = u[4];
+            const T du = u[5] - u[4], r = u[4] - ref;  // phi along x, and above ref
+            const T x0 = r + du * bx.w[1] + u[6] * bx.w[2] + u[7] * bx.w[3];
+            const T x1 = du * bx.dw[1] + u[6] * bx.dw[2] + u[7] * bx.dw[3];
+            T x2 = T(0);
+            if constexpr (SECOND) x2 = du * bx.ddw[1] + u[6] * bx.ddw[2] + u[7] * bx.ddw[3];
+            sums(A[0], vy == 0, x0, x1, x2, by.w[vy], by.dw[vy], SECOND ? by.ddw[vy] : T(0));
+            add(A[0], false, u, by.w[2 + vy], by.dw[2 + vy], SECOND ? by.ddw[2 + vy] : T(0));
+        }
+    };
+    T h = 0, hx = 0, hy = 0, hz = 0;
+    T hxx = 0, hyy = 0, hzz = 0, hxy = 0, hxz = 0, hyz = 0;
+    auto reduce = [&](const Acc &a, int kz) {
+        h += a.a00 * bz.w[kz];
+        hx += a.a10 * bz.w[kz];
+        hy += a.a01 * bz.w[kz];
+        hz += a.a00 * bz.dw[kz];
+        if constexpr (SECOND) {
+            hxx += a.a20 * bz.w[kz];
+            hxy += a.a11 * bz.w[kz];
+            hyy += a.a02 * bz.w[kz];
+            hxz += a.a10 * bz.dw[kz];
+            hyz += a.a01 * bz.dw[kz];
+            hzz += a.a00 * bz.ddw[kz];
+        }
+    };
+    // A group's loads are issued before the previous group's sums, and the sums
+    // are pinned there: left to itself the compiler issues all 64 loads first
+    // and holds their values (the FP32 vector potential then spills).
+    T u[2][8];
+    load(0, u[0]);
+#pragma unroll
+    for (int q = 0; q < 8; q++) {
+        if (q < 7) load(q + 1, u[(q + 1) & 1]);
+        sum(q, u[q & 1]);
+        asm volatile("" : "+v"(A[0].a00), "+v"(A[0].a10), "+v"(A[0].a01), "+v"(A[1].a00),
+                     "+v"(A[1].a10), "+v"(A[1].a01));
+        if ((q & 3) == 3) {
+            reduce(A[0], q >> 2);
+            reduce(A[1], 2 + (q >> 2));
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    H = ref + h;
+    G[0] = hx; G[1] = hy; G[2] = hz;
+    if constexpr (SECOND) {
+        Hs[0] = hxx; Hs[1] = hxy; Hs[2] = hxz;
+        Hs[3] = hxy; Hs[4] = hyy; Hs[5] = hyz;
+        Hs[6] = hxz; Hs[7] = hyz; Hs[8] = hzz;
+    }
+}
+
+// Value and gradient of the tricubic of cell c at local coordinates xi, for
+// any cross-derivative rule.
+template <typename T, int MIX>
+__device__ __forceinline__ void tricubic(const Geom &g, Rsrc rphi, Rsrc rgx, Rsrc rgy, Rsrc rgz,
+                                         const int *c, const T *xi, T &H, T *G)
+{
+    if constexpr (MIX == GALS_MIXED_CENTRAL) {
+        tricubic_central<T, false>(g, rphi, rgx, rgy, rgz, c, xi, H, G, nullptr);
+    } else {
+        T d[8][8];
+        gather3d<T, MIX>(g, rphi, rgx, rgy, rgz, c[0], c[1], c[2], d);
+        Basis<T> b[3];
+#pragma unroll
+        for (int a = 0; a < 3; a++) basis<T, false>(xi[a], geo_h<T>(g, a), geo_ih<T>(g, a), b[a]);
+        hermite3d(d, b[0], b[1], b[2], H, G[0], G[1], G[2]);
+    }
 }
 
 }  // namespace gals

@@ -509,7 +509,7 @@ inline unsigned band_blocks3d(const Geom &g)
 }
 
 // 3D step for an affine field: the foot from the host's map, one thread per
-// node, the 64-value gather through the caches.
+// node, the gather through the caches.
 template <typename T, int MIX, int PSI>
 __global__ __launch_bounds__(kBlock) void k_step3d_affine(Geom g, AffineMap<T> am, double dt,
                                                           const T *__restrict__ phi,
@@ -529,15 +529,10 @@ __global__ __launch_bounds__(kBlock) void k_step3d_affine(Geom g, AffineMap<T> a
     bool outb[3];
     split_cells<T, 3>(g, sc, cell, xi, outb);
     const T *gx = grad, *gy = grad + g.plane, *gz = grad + 2 * g.plane;
-    T d[8][8];
-    gather3d<T, MIX>(g, plane_rsrc(phi, g.plane), plane_rsrc(gx, g.plane), plane_rsrc(gy, g.plane),
-                     plane_rsrc(gz, g.plane), cell[0], cell[1], cell[2], d);
-    Basis<T> bx, by, bz;
-    basis<T, false>(xi[0], geo_h<T>(g, 0), geo_ih<T>(g, 0), bx);
-    basis<T, false>(xi[1], geo_h<T>(g, 1), geo_ih<T>(g, 1), by);
-    basis<T, false>(xi[2], geo_h<T>(g, 2), geo_ih<T>(g, 2), bz);
-    T H, Hx, Hy, Hz;
-    hermite3d(d, bx, by, bz, H, Hx, Hy, Hz);
+    T H, G[3];
+    tricubic<T, MIX>(g, plane_rsrc(phi, g.plane), plane_rsrc(gx, g.plane), plane_rsrc(gy, g.plane),
+                     plane_rsrc(gz, g.plane), cell, xi, H, G);
+    T Hx = G[0], Hy = G[1], Hz = G[2];
     if (outb[0]) Hx = T(0);
     if (outb[1]) Hy = T(0);
     if (outb[2]) Hz = T(0);
@@ -560,7 +555,7 @@ __global__ __launch_bounds__(kBlock) void k_step3d_affine(Geom g, AffineMap<T> a
 }
 
 // The part of a 3D step after the trace: boundary treatment of the foot,
-// split, 64-value gather, tricubic value and gradient, gradient update.
+// split, gather, tricubic value and gradient, gradient update.
 template <typename T, int KIND, int MIX, int PSI>
 __device__ __forceinline__ void finish3d(const Geom &g, const Vel<T> &p, const Stage<T> &st,
                                          double dt, int i, int j, int k, double *X, const T *J,
@@ -571,18 +566,13 @@ __device__ __forceinline__ void finish3d(const Geom &g, const Vel<T> &p, const S
     const unsigned out = project_foot<3>(g, X);
 
     int cell[3];
-    double xi[3];
-    split<3>(g, X, cell, xi);
-
-    T d[8][8];
-    gather3d<T, MIX>(g, plane_rsrc(phi, g.plane), plane_rsrc(gx, g.plane), plane_rsrc(gy, g.plane),
-                     plane_rsrc(gz, g.plane), cell[0], cell[1], cell[2], d);
-    Basis<T> bx, by, bz;
-    basis<T, false>(T(xi[0]), geo_h<T>(g, 0), geo_ih<T>(g, 0), bx);
-    basis<T, false>(T(xi[1]), geo_h<T>(g, 1), geo_ih<T>(g, 1), by);
-    basis<T, false>(T(xi[2]), geo_h<T>(g, 2), geo_ih<T>(g, 2), bz);
-    T H, Hx, Hy, Hz;
-    hermite3d(d, bx, by, bz, H, Hx, Hy, Hz);
+    double xid[3];
+    split<3>(g, X, cell, xid);
+    const T xi[3] = {T(xid[0]), T(xid[1]), T(xid[2])};
+    T H, gradH[3];
+    tricubic<T, MIX>(g, plane_rsrc(phi, g.plane), plane_rsrc(gx, g.plane), plane_rsrc(gy, g.plane),
+                     plane_rsrc(gz, g.plane), cell, xi, H, gradH);
+    T Hx = gradH[0], Hy = gradH[1], Hz = gradH[2];
     if (out & 1u) Hx = T(0);
     if (out & 2u) Hy = T(0);
     if (out & 4u) Hz = T(0);
@@ -699,9 +689,9 @@ __device__ __forceinline__ void stage_vecpot(const Vel<T> &p, T (*tab)[kBlock], 
     modes_at<T, LDS>(p, tab, sx, cx, sy, cy, sz, cz, T(1), w, R);
 }
 
-// Five waves per SIMD for the FP32 superconsistent kernel: about 93 VGPRs
-// without spills (six waves would spill); the FP64 and Heun kernels need more
-// registers and keep the compiler's choice.
+// At least five waves per SIMD for the FP32 superconsistent kernel (79 VGPRs,
+// six waves; its 24 KB of LDS a block allow six too); the FP64 and Heun kernels
+// need more registers and keep the compiler's choice.
 template <typename T, int MIX, bool SHIFT, int PSI>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
     sizeof(T) == 4 && PSI == GALS_PSI_SUPERCONSISTENT ? 5 : 1))) void k_step3d_vecpot(
