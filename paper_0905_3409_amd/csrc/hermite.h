@@ -200,6 +200,42 @@ __device__ __forceinline__ double bload(Rsrc r, unsigned elem, double)
     return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, elem * 8u, 0, 0));
 }
 
+// Two (four) consecutive elements from `elem` on, as one or two wide loads.
+template <typename T, int N>
+using Vec = T __attribute__((ext_vector_type(N)));
+
+__device__ __forceinline__ void bload2(Rsrc r, unsigned elem, float *u)
+{
+    const auto v =
+        __builtin_bit_cast(Vec<float, 2>, __builtin_amdgcn_raw_buffer_load_b64(r, elem * 4u, 0, 0));
+    u[0] = v.x;
+    u[1] = v.y;
+}
+
+__device__ __forceinline__ void bload2(Rsrc r, unsigned elem, double *u)
+{
+    const auto v =
+        __builtin_bit_cast(Vec<double, 2>, __builtin_amdgcn_raw_buffer_load_b128(r, elem * 8u, 0, 0));
+    u[0] = v.x;
+    u[1] = v.y;
+}
+
+__device__ __forceinline__ void bload4(Rsrc r, unsigned elem, float *u)
+{
+    const auto v =
+        __builtin_bit_cast(Vec<float, 4>, __builtin_amdgcn_raw_buffer_load_b128(r, elem * 4u, 0, 0));
+    u[0] = v.x;
+    u[1] = v.y;
+    u[2] = v.z;
+    u[3] = v.w;
+}
+
+__device__ __forceinline__ void bload4(Rsrc r, unsigned elem, double *u)
+{
+    bload2(r, elem, u);
+    bload2(r, elem + 2u, u + 2);
+}
+
 // Store element `elem` of a plane through a 32-bit byte offset (every plane
 // is below 2 GiB), so the address is the plane's scalar base plus one vector
 // offset.
@@ -606,11 +642,24 @@ __device__ __forceinline__ void tricubic_central(const Geom &g, Rsrc rphi, Rsrc 
         stencil_weights(bx.ddw, i2hx, xlo, xhi, sx.ddw);
         stencil_weights(by.ddw, i2hy, ylo, yhi, sy.ddw);
     }
-    // byte offsets are formed by bload; a node outside the grid repeats its
-    // neighbour (its weight is 0), so padding is never read
     const unsigned P = unsigned(g.pitch), S = unsigned(g.pitch) * unsigned(g.n[1]);
     const unsigned o0 = unsigned(c[2]) * S + unsigned(c[1]) * P + unsigned(c[0]);
-    const unsigned xm = xlo ? 0u : 1u, xp = xhi ? 0u : 1u;  // steps to c - 1 and from c + 1
+    // A row's four x nodes are one window of wide loads: c - 1 .. c + 2, or
+    // 0 .. 3 at the first cell, whose weights move down by one. The window's
+    // last value belongs to no stencil at the first cell and lies past the row
+    // at the last one (in the padding, the next row, or past the plane, where
+    // a buffer load gives 0): it is replaced by 0 there, whatever it holds.
+    // Rows past the grid repeat their neighbour with weight 0.
+    const unsigned xm = xlo ? 0u : 1u;
+    const bool xedge = xlo || xhi;
+    if (xlo) {
+#pragma unroll
+        for (int k = 0; k < 3; k++) {
+            sx.w[k] = sx.w[k + 1];
+            sx.dw[k] = sx.dw[k + 1];
+            if constexpr (SECOND) sx.ddw[k] = sx.ddw[k + 1];
+        }
+    }
     const unsigned ym = ylo ? 0u : P, yp = yhi ? 0u : P;
     const unsigned row[4] = {o0 - ym, o0, o0 + P, o0 + P + yp};
 
@@ -623,23 +672,12 @@ __device__ __forceinline__ void tricubic_central(const Geom &g, Rsrc rphi, Rsrc 
         const int part = q & 3;
         if (part < 2) {
 #pragma unroll
-            for (int r = 0; r < 2; r++) {
-                const unsigned o = row[2 * part + r] + zo;
-                u[4 * r] = bload(rgz, o - xm, T());
-                u[4 * r + 1] = bload(rgz, o, T());
-                u[4 * r + 2] = bload(rgz, o + 1u, T());
-                u[4 * r + 3] = bload(rgz, o + 1u + xp, T());
-            }
+            for (int r = 0; r < 2; r++) bload4(rgz, row[2 * part + r] + zo - xm, u + 4 * r);
         } else {
             const unsigned o = row[part - 1] + zo;
-            u[0] = bload(rgy, o - xm, T());
-            u[1] = bload(rgy, o, T());
-            u[2] = bload(rgy, o + 1u, T());
-            u[3] = bload(rgy, o + 1u + xp, T());
-            u[4] = bload(rphi, o, T());
-            u[5] = bload(rphi, o + 1u, T());
-            u[6] = bload(rgx, o, T());
-            u[7] = bload(rgx, o + 1u, T());
+            bload4(rgy, o - xm, u);
+            bload2(rphi, o, u + 4);
+            bload2(rgx, o, u + 6);
         }
     };
     // a[dx dy]: sums over x and y of one plane's samples, derivative orders dx
@@ -660,7 +698,8 @@ __device__ __forceinline__ void tricubic_central(const Geom &g, Rsrc rphi, Rsrc 
             a.a20 = first ? x2 * wy : a.a20 + x2 * wy;
         }
     };
-    auto add = [&](Acc &a, bool first, const T *u, T wy, T dwy, T ddwy) {
+    auto add = [&](Acc &a, bool first, const T *w, T wy, T dwy, T ddwy) {
+        const T u[4] = {w[0], w[1], w[2], xedge ? T(0) : w[3]};
         sums(a, first, dot(u, sx.w), dot(u, sx.dw), SECOND ? dot(u, sx.ddw) : T(0), wy, dwy, ddwy);
     };
     auto sum = [&](int q, const T *u) {

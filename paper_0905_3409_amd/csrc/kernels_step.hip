@@ -596,7 +596,8 @@ __device__ __forceinline__ void finish3d(const Geom &g, const Vel<T> &p, const S
 }
 
 template <typename T, int KIND, int MIX, int PSI>
-__global__ __launch_bounds__(kBlock) void k_step3d(Geom g, Vel<T> p, Stage<T> st, double dt,
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
+    PSI != GALS_PSI_SUPERCONSISTENT ? 1 : sizeof(T) == 4 ? 5 : 3))) void k_step3d(Geom g, Vel<T> p, Stage<T> st, double dt,
                                                    const T *__restrict__ phi,
                                                    const T *__restrict__ grad,
                                                    T *__restrict__ phi_o, T *__restrict__ grad_o)
@@ -689,12 +690,13 @@ __device__ __forceinline__ void stage_vecpot(const Vel<T> &p, T (*tab)[kBlock], 
     modes_at<T, LDS>(p, tab, sx, cx, sy, cy, sz, cz, T(1), w, R);
 }
 
-// At least five waves per SIMD for the FP32 superconsistent kernel (79 VGPRs,
-// six waves; its 24 KB of LDS a block allow six too); the FP64 and Heun kernels
-// need more registers and keep the compiler's choice.
+// At least five waves per SIMD for the superconsistent kernel in FP32, three in
+// FP64 (150 VGPRs; at the compiler's choice of 170 two waves, 480 against 375 us
+// for two steps of 141 x 131 x 121 nodes); the Heun kernels need more registers
+// and keep the compiler's choice.
 template <typename T, int MIX, bool SHIFT, int PSI>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
-    sizeof(T) == 4 && PSI == GALS_PSI_SUPERCONSISTENT ? 5 : 1))) void k_step3d_vecpot(
+    PSI != GALS_PSI_SUPERCONSISTENT ? 1 : sizeof(T) == 4 ? 5 : 3))) void k_step3d_vecpot(
     Geom g, Vel<T> p, Stage<T> st,
                                                           double dt, const T *__restrict__ tab,
                                                           const T *__restrict__ phi,
