@@ -92,21 +92,37 @@ struct DeviceGuard {
 
 double time_factor(double period, double t) { return period > 0.0 ? cos(M_PI * t / period) : 1.0; }
 
-// Stream-function tables into the workspace (sine stream functions only).
-hipError_t launch_tables(const gals_ctx *ctx, void *workspace, hipStream_t s)
+// Whether the steps of an advance of `steps` steps read the per-axis sin/cos
+// table. The vector potential always does. The vortex in FP64 and the 3D
+// deformation field take it from 2^21 node-steps on, else their kernels form
+// the node's own angles: the table saves them about 1 us per 2^20 node-steps
+// and its launch costs 2.5 to 3 us (64^2 vortex, 8 steps 40 us without, 43
+// with; 101^3 deformation field, 8 steps 307 without, 299 with).
+bool axis_tables(const gals_ctx *ctx, int64_t steps)
+{
+    if (ctx->vel_kind == GALS_VEL_VECPOT_SIN) return true;
+    const bool trig = ctx->vel_kind == GALS_VEL_LEVEQUE3D ||
+                      (ctx->vel_kind == GALS_VEL_VORTEX && ctx->prec == GALS_F64);
+    return trig && double(ctx->g.nodes) * double(steps) >= double(1 << 21);
+}
+
+// Velocity tables of the field into the workspace.
+hipError_t launch_tables(const gals_ctx *ctx, int64_t steps, void *workspace, hipStream_t s)
 {
     char *ws = (char *)workspace;
-    if (ctx->dim == 3 && ctx->vel_kind == GALS_VEL_VECPOT_SIN)
+    if (axis_tables(ctx, steps))
         return launch_axis_tables(ctx, ws + axistab_offset(ctx), s);
     if (ctx->vel_kind != GALS_VEL_STREAM_SIN) return hipSuccess;
     return launch_stream_tables(ctx, ws + coltab_offset(ctx), ws + rowtab_offset(ctx), s);
 }
 
-// Steps n_begin .. n_end-1 of an advance from time t0 (step n starts at
-// t0 + n dt), ping-ponging through the workspace's state copy; the result
-// ends in (phi, grad). The tables must be in the workspace already.
+// Steps n_begin .. n_end-1 of an advance of `steps` steps from time t0 (step n
+// starts at t0 + n dt), ping-ponging through the workspace's state copy; the
+// result ends in (phi, grad). The tables (launch_tables with the same `steps`)
+// must be in the workspace already.
 hipError_t advance_core(const gals_ctx *ctx, void *phi, void *grad, double t0, double dt,
-                        int64_t n_begin, int64_t n_end, void *workspace, hipStream_t s)
+                        int64_t n_begin, int64_t n_end, int64_t steps, void *workspace,
+                        hipStream_t s)
 {
     const size_t pb = size_t(ctx->g.plane) * elem_size(ctx);
     char *ws = (char *)workspace;
@@ -115,7 +131,7 @@ hipError_t advance_core(const gals_ctx *ctx, void *phi, void *grad, double t0, d
     if (ctx->vel_kind == GALS_VEL_STREAM_SIN) {
         coltab = ws + coltab_offset(ctx);
         rowtab = ws + rowtab_offset(ctx);
-    } else if (ctx->dim == 3 && ctx->vel_kind == GALS_VEL_VECPOT_SIN) {
+    } else if (axis_tables(ctx, steps)) {
         coltab = ws + axistab_offset(ctx);  // the per-axis sin/cos table
     }
     hipError_t e = hipSuccess;
@@ -442,8 +458,8 @@ int gals_advance(gals_ctx *ctx, void *phi, void *grad, double t0, double dt, int
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "gals_advance: pending HIP error");
     hipStream_t s = (hipStream_t)stream;
-    e = launch_tables(ctx, workspace, s);
-    if (e == hipSuccess) e = advance_core(ctx, phi, grad, t0, dt, 0, steps, workspace, s);
+    e = launch_tables(ctx, steps, workspace, s);
+    if (e == hipSuccess) e = advance_core(ctx, phi, grad, t0, dt, 0, steps, steps, workspace, s);
     return e == hipSuccess ? GALS_OK : hip_fail(e, "gals_advance: launch");
 }
 
@@ -477,8 +493,8 @@ int gals_advance_noalloc(gals_ctx *ctx, void *phi, void *grad, double t0, double
     e = scratch_address(ctx->device, &ws);
     if (e != hipSuccess) return hip_fail(e, "gals_advance_noalloc: hipGetSymbolAddress");
     hipStream_t s = (hipStream_t)stream;
-    e = launch_tables(ctx, ws, s);
-    if (e == hipSuccess) e = advance_core(ctx, phi, grad, t0, dt, 0, steps, ws, s);
+    e = launch_tables(ctx, steps, ws, s);
+    if (e == hipSuccess) e = advance_core(ctx, phi, grad, t0, dt, 0, steps, steps, ws, s);
     return e == hipSuccess ? GALS_OK : hip_fail(e, "gals_advance_noalloc: launch");
 }
 
@@ -669,12 +685,12 @@ int gals_advance_save(gals_ctx *ctx, void *phi, void *grad, double t0, double dt
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "gals_advance_save: pending HIP error");
     hipStream_t s = (hipStream_t)stream;
-    e = launch_tables(ctx, workspace, s);
+    e = launch_tables(ctx, steps, workspace, s);
     for (int64_t k = 0; k < nsegments(steps, every) && e == hipSuccess; k++) {
         char *slot = (char *)ckpt + size_t(k) * seg_state_bytes(ctx);
         e = copy_state(ctx, slot, slot + pb, phi, grad, s);
         const int64_t n0 = k * every, n1 = n0 + every < steps ? n0 + every : steps;
-        if (e == hipSuccess) e = advance_core(ctx, phi, grad, t0, dt, n0, n1, workspace, s);
+        if (e == hipSuccess) e = advance_core(ctx, phi, grad, t0, dt, n0, n1, steps, workspace, s);
     }
     return e == hipSuccess ? GALS_OK : hip_fail(e, "gals_advance_save: launch");
 }
@@ -719,7 +735,7 @@ int gals_adjoint(gals_ctx *ctx, const void *ckpt, size_t ckpt_bytes, double t0, 
     double *part = (double *)(ws + adj_part_offset(ctx, every));
     const int nblocks = int(adjoint_blocks(ctx));
     void *coltab = ws + coltab_offset(ctx), *rowtab = ws + rowtab_offset(ctx);
-    e = launch_tables(ctx, workspace, s);
+    e = launch_tables(ctx, 1, workspace, s);
     if (e == hipSuccess) e = launch_zero(part, int64_t(nblocks) * 16, s);
     if (e == hipSuccess) e = launch_zero(dS, 16, s);
     // each adjoint step zeroes the buffer it reads, which then receives the
@@ -789,7 +805,7 @@ int gals_adjoint_step(gals_ctx *ctx, const void *phi, const void *grad, double t
     char *ws = (char *)workspace;
     double *part = (double *)(ws + adj_part_offset(ctx, 1));
     const int nblocks = int(adjoint_blocks(ctx));
-    e = launch_tables(ctx, workspace, s);
+    e = launch_tables(ctx, 1, workspace, s);
     if (e == hipSuccess) e = launch_zero(part, int64_t(nblocks) * 16, s);
     if (e == hipSuccess) e = launch_zero(lam_out, 3 * ctx->g.plane, s);
     if (e == hipSuccess)

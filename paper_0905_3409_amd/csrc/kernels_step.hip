@@ -18,6 +18,7 @@ namespace gals {
 // count below 2^31).
 template <typename T, int KIND, int MIX, int PSI>
 __global__ __launch_bounds__(kBlock) void k_step2d(Geom g, Vel<T> p, Stage<T> st, double dt,
+                                                   const T *__restrict__ tab,
                                                    const T *__restrict__ phi,
                                                    const T *__restrict__ grad,
                                                    T *__restrict__ phi_o, T *__restrict__ grad_o)
@@ -34,7 +35,12 @@ __global__ __launch_bounds__(kBlock) void k_step2d(Geom g, Vel<T> p, Stage<T> st
     const double x[2] = {node_coord(g.lo[0], i, g.h[0]), node_coord(g.lo[1], j, g.h[1])};
     double X[2];
     T J[4];  // superconsistent Jacobian, or (Heun) grad v at the node
-    trace<T, 2, KIND, PSI == GALS_PSI_SUPERCONSISTENT>(p, st, dt, x, X, J);
+    if constexpr (kTrigField<KIND> && sizeof(T) == 8) {
+        const int64_t ti[2] = {i, int64_t(g.n[0]) + j};
+        trace_trig<T, 2, KIND, PSI == GALS_PSI_SUPERCONSISTENT>(st, tab, ti, x, X, J);
+    } else {
+        trace<T, 2, KIND, PSI == GALS_PSI_SUPERCONSISTENT>(p, st, dt, x, X, J);
+    }
     const unsigned out = project_foot<2>(g, X);
 
     int cell[2];
@@ -598,6 +604,7 @@ __device__ __forceinline__ void finish3d(const Geom &g, const Vel<T> &p, const S
 template <typename T, int KIND, int MIX, int PSI>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
     PSI != GALS_PSI_SUPERCONSISTENT ? 1 : sizeof(T) == 4 ? 5 : 3))) void k_step3d(Geom g, Vel<T> p, Stage<T> st, double dt,
+                                                   const T *__restrict__ tab,
                                                    const T *__restrict__ phi,
                                                    const T *__restrict__ grad,
                                                    T *__restrict__ phi_o, T *__restrict__ grad_o)
@@ -609,7 +616,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
                          node_coord(g.lo[2], k, g.h[2])};
     double X[3];
     T J[9];
-    trace<T, 3, KIND, PSI == GALS_PSI_SUPERCONSISTENT>(p, st, dt, x, X, J);
+    const int64_t ti[3] = {i, int64_t(g.n[0]) + j, int64_t(g.n[0]) + g.n[1] + k};
+    trace_trig<T, 3, KIND, PSI == GALS_PSI_SUPERCONSISTENT>(st, tab, ti, x, X, J);
     finish3d<T, KIND, MIX, PSI>(g, p, st, dt, i, j, k, X, J, phi, grad, phi_o, grad_o);
 }
 
@@ -843,7 +851,7 @@ static hipError_t launch_vecpot(const gals_ctx *ctx, const Vel<T> &p, const void
 template <typename T, int KIND, int MIX, int PSI>
 static hipError_t launch_typed(const gals_ctx *ctx, const Vel<T> &p, const void *phi,
                                const void *grad, void *phi_o, void *grad_o, double dt, double c1,
-                               double c2, double c3, hipStream_t s)
+                               double c2, double c3, const void *tab, hipStream_t s)
 {
     const Stage<T> st = make_stage<T>(dt, c1, c2, c3);
     // rounded up to a multiple of 8 for the XCD band mapping (xcd_block)
@@ -865,18 +873,17 @@ static hipError_t launch_typed(const gals_ctx *ctx, const Vel<T> &p, const void 
         return hipGetLastError();
     }
     if (ctx->dim == 2) {
-        if constexpr (KIND == GALS_VEL_STREAM_SIN || KIND == GALS_VEL_VORTEX ||
-                      KIND == GALS_VEL_PSEUDO1D) {
+        if constexpr (KIND == GALS_VEL_VORTEX || KIND == GALS_VEL_PSEUDO1D) {
             hipLaunchKernelGGL((k_step2d<T, KIND, MIX, PSI>), dim3(blocks), dim3(kBlock), 0, s,
-                               ctx->g, p, st, dt, (const T *)phi, (const T *)grad, (T *)phi_o,
+                               ctx->g, p, st, dt, (const T *)tab, (const T *)phi, (const T *)grad, (T *)phi_o,
                                (T *)grad_o);
             return hipGetLastError();
         }
     } else {
-        if constexpr (KIND == GALS_VEL_VECPOT_SIN || KIND == GALS_VEL_LEVEQUE3D) {
+        if constexpr (KIND == GALS_VEL_LEVEQUE3D) {
             hipLaunchKernelGGL((k_step3d<T, KIND, MIX, PSI>), dim3(band_blocks3d(ctx->g)),
                                dim3(kBlock), 0, s,
-                               ctx->g, p, st, dt, (const T *)phi, (const T *)grad, (T *)phi_o,
+                               ctx->g, p, st, dt, (const T *)tab, (const T *)phi, (const T *)grad, (T *)phi_o,
                                (T *)grad_o);
             return hipGetLastError();
         }
@@ -887,15 +894,14 @@ static hipError_t launch_typed(const gals_ctx *ctx, const Vel<T> &p, const void 
 template <typename T, int MIX, int PSI>
 static hipError_t launch_kind(const gals_ctx *ctx, const Vel<T> &p, const void *phi,
                               const void *grad, void *phi_o, void *grad_o, double dt, double c1,
-                              double c2, double c3, hipStream_t s)
+                              double c2, double c3, const void *tab, hipStream_t s)
 {
 #define GALS_KIND_CASE(K)                                                                         \
     case K:                                                                                       \
-        return launch_typed<T, K, MIX, PSI>(ctx, p, phi, grad, phi_o, grad_o, dt, c1, c2, c3, s);
+        return launch_typed<T, K, MIX, PSI>(ctx, p, phi, grad, phi_o, grad_o, dt, c1, c2, c3, tab, \
+                                            s);
     switch (ctx->vel_kind) {
         GALS_KIND_CASE(GALS_VEL_AFFINE)
-        GALS_KIND_CASE(GALS_VEL_STREAM_SIN)
-        GALS_KIND_CASE(GALS_VEL_VECPOT_SIN)
         GALS_KIND_CASE(GALS_VEL_VORTEX)
         GALS_KIND_CASE(GALS_VEL_PSEUDO1D)
         GALS_KIND_CASE(GALS_VEL_LEVEQUE3D)
@@ -941,9 +947,9 @@ hipError_t launch_step(const gals_ctx *ctx, const void *phi, const void *grad, v
                                                          dt, c1, c2, c3, coltab, rowtab, s);
         return ctx->prec == GALS_F32
                    ? launch_kind<float, MIX, PSI>(ctx, ctx->vf, phi, grad, phi_o, grad_o, dt, c1,
-                                                  c2, c3, s)
+                                                  c2, c3, coltab, s)
                    : launch_kind<double, MIX, PSI>(ctx, ctx->vd, phi, grad, phi_o, grad_o, dt, c1,
-                                                   c2, c3, s);
+                                                   c2, c3, coltab, s);
     });
 }
 

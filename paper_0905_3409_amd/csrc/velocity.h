@@ -82,6 +82,36 @@ __device__ __forceinline__ void shifted_sincos_long(T s1, T c1, T d, T &s, T &c)
     c = c1 * cd - s1 * sd;
 }
 
+// The FP64 series one term longer (to a^11 and a^12): the dropped terms stay
+// below 7e-19 up to |pi d| = 0.2, for fields run at a few cells per step on
+// coarse grids. FP32 takes shifted_sincos_long.
+template <typename T>
+constexpr double kShiftMaxWide = sizeof(T) == 8 ? 0.2 : kShiftMaxLong<T>;
+template <typename T>
+__device__ __forceinline__ void shifted_sincos_wide(T s1, T c1, T d, T &s, T &c)
+{
+    if constexpr (sizeof(T) == 4) {
+        shifted_sincos_long(s1, c1, d, s, c);
+    } else {
+        const T a = T(kPi) * d, a2 = a * a;
+        const T sd =
+            a * (T(1) -
+                 a2 * (T(1.0 / 6) -
+                       a2 * (T(1.0 / 120) -
+                             a2 * (T(1.0 / 5040) -
+                                   a2 * (T(1.0 / 362880) - a2 * T(1.0 / 39916800))))));
+        const T cd =
+            T(1) -
+            a2 * (T(0.5) -
+                  a2 * (T(1.0 / 24) -
+                        a2 * (T(1.0 / 720) -
+                              a2 * (T(1.0 / 40320) -
+                                    a2 * (T(1.0 / 3628800) - a2 * T(1.0 / 479001600))))));
+        s = s1 * cd + c1 * sd;
+        c = c1 * cd - s1 * sd;
+    }
+}
+
 template <typename T>
 __device__ __forceinline__ T pick4(const T a[4], int i)
 {
@@ -221,16 +251,13 @@ __device__ __forceinline__ void vel_stream(const Params &p, const double *x, T c
     stream_modes(p, sx, cx, sy, cy, c, v, J);
 }
 
-// s = sin^2(pi x) sin^2(pi y) / pi.
+// s = sin^2(pi x) sin^2(pi y) / pi, from sin and cos of pi x and pi y.
 template <typename T>
-__device__ __forceinline__ void vel_vortex(const double *x, T c, T *v, T *J)
+__device__ __forceinline__ void vortex_from(const T *s1, const T *c1, T c, T *v, T *J)
 {
-    T s1x, c1x, s1y, c1y;
-    sincospi_t(T(x[0]), &s1x, &c1x);
-    sincospi_t(T(x[1]), &s1y, &c1y);
-    const T qx = s1x * s1x, qy = s1y * s1y;             // sin^2
-    const T s2x = T(2) * s1x * c1x, s2y = T(2) * s1y * c1y;  // sin(2 pi .)
-    const T c2x = T(1) - T(2) * qx, c2y = T(1) - T(2) * qy;  // cos(2 pi .)
+    const T qx = s1[0] * s1[0], qy = s1[1] * s1[1];                          // sin^2
+    const T s2x = T(2) * s1[0] * c1[0], s2y = T(2) * s1[1] * c1[1];          // sin(2 pi .)
+    const T c2x = T(1) - T(2) * qx, c2y = T(1) - T(2) * qy;                  // cos(2 pi .)
     const T pi = T(kPi);
     from_stream(s2x * qy, qx * s2y, T(2) * pi * c2x * qy, pi * s2x * s2y, T(2) * pi * qx * c2y,
                 c, v, J);
@@ -355,30 +382,43 @@ __device__ __forceinline__ void vel_vecpot(const Vel<T> &p, const double *x, T c
 
 // Divergence-free reading of the 3D deformation field of sec. 6.2:
 // u = 2 sin^2(pi x) sin(2 pi y) sin(2 pi z), v = -sin(2 pi x) sin^2(pi y) sin(2 pi z),
-// w = -sin(2 pi x) sin(2 pi y) sin^2(pi z).
+// w = -sin(2 pi x) sin(2 pi y) sin^2(pi z), from sin and cos of pi x, pi y, pi z.
 template <typename T>
-__device__ __forceinline__ void vel_leveque(const double *x, T c, T *v, T *J)
+__device__ __forceinline__ void leveque_from(const T *s1, const T *c1, T c, T *v, T *J)
 {
-    T s1[3], c1[3], q[3], s2[3], c2[3];
+    const T tpi = T(2 * kPi);
+    T q[3], s2[3], c2[3];  // sin^2, sin(2 pi .), 2 pi cos(2 pi .)
     for (int i = 0; i < 3; i++) {
-        sincospi_t(T(x[i]), &s1[i], &c1[i]);
         q[i] = s1[i] * s1[i];
         s2[i] = T(2) * s1[i] * c1[i];
-        c2[i] = T(1) - T(2) * q[i];
+        c2[i] = tpi - (T(2) * tpi) * q[i];
     }
-    const T pi = T(kPi), tpi = T(2 * kPi);
-    v[0] = c * T(2) * q[0] * s2[1] * s2[2];
-    v[1] = -c * s2[0] * q[1] * s2[2];
-    v[2] = -c * s2[0] * s2[1] * q[2];
-    J[0] = c * tpi * s2[0] * s2[1] * s2[2];        // du/dx
-    J[1] = c * T(2) * q[0] * tpi * c2[1] * s2[2];  // du/dy
-    J[2] = c * T(2) * q[0] * s2[1] * tpi * c2[2];  // du/dz
-    J[3] = -c * tpi * c2[0] * q[1] * s2[2];        // dv/dx
-    J[4] = -c * s2[0] * pi * s2[1] * s2[2];        // dv/dy
-    J[5] = -c * s2[0] * q[1] * tpi * c2[2];        // dv/dz
-    J[6] = -c * tpi * c2[0] * s2[1] * q[2];        // dw/dx
-    J[7] = -c * s2[0] * tpi * c2[1] * q[2];        // dw/dy
-    J[8] = -c * s2[0] * s2[1] * pi * s2[2];        // dw/dz
+    const T u = T(2) * c * q[0], w = -c * s2[0];
+    const T uz = u * s2[2], uy = u * s2[1], wy = w * q[1], wz = w * q[2];
+    const T d = -c * c2[0], p = (T(kPi) * w) * (s2[1] * s2[2]);
+    v[0] = uz * s2[1];
+    v[1] = wy * s2[2];
+    v[2] = wz * s2[1];
+    J[0] = T(-2) * p;         // du/dx
+    J[1] = uz * c2[1];        // du/dy
+    J[2] = uy * c2[2];        // du/dz
+    J[3] = d * q[1] * s2[2];  // dv/dx
+    J[4] = p;                 // dv/dy
+    J[5] = wy * c2[2];        // dv/dz
+    J[6] = d * q[2] * s2[1];  // dw/dx
+    J[7] = wz * c2[1];        // dw/dy
+    J[8] = p;                 // dw/dz
+}
+
+// Fields that are functions of sin and cos of the coordinate angles alone.
+template <int KIND>
+constexpr bool kTrigField = KIND == GALS_VEL_VORTEX || KIND == GALS_VEL_LEVEQUE3D;
+
+template <typename T, int KIND>
+__device__ __forceinline__ void trig_field(const T *s1, const T *c1, T c, T *v, T *J)
+{
+    if constexpr (KIND == GALS_VEL_VORTEX) vortex_from(s1, c1, c, v, J);
+    else leveque_from(s1, c1, c, v, J);
 }
 
 // Dispatch on the compile-time field kind (D = space dimension).
@@ -391,12 +431,13 @@ __device__ __forceinline__ void velocity(const Vel<T> &p, const double *x, T c, 
         vel_stream(p, x, c, v, J);
     } else if constexpr (KIND == GALS_VEL_VECPOT_SIN) {
         vel_vecpot(p, x, c, v, J);
-    } else if constexpr (KIND == GALS_VEL_VORTEX) {
-        vel_vortex(x, c, v, J);
     } else if constexpr (KIND == GALS_VEL_PSEUDO1D) {
         vel_pseudo1d(x, c, v, J);
     } else {
-        vel_leveque(x, c, v, J);
+        T s1[D], c1[D];
+#pragma unroll
+        for (int a = 0; a < D; a++) sincospi_t(T(x[a]), &s1[a], &c1[a]);
+        trig_field<T, KIND>(s1, c1, c, v, J);
     }
 }
 
