@@ -135,19 +135,40 @@ hipError_t advance_core(const gals_ctx *ctx, void *phi, void *grad, double t0, d
         coltab = ws + axistab_offset(ctx);  // the per-axis sin/cos table
     }
     hipError_t e = hipSuccess;
-    for (int64_t n = n_begin; n < n_end; n++) {
-        const double t = t0 + double(n) * dt;
-        const double c1 = time_factor(ctx->period, t + dt);
-        const double c2 = time_factor(ctx->period, t);
-        const double c3 = time_factor(ctx->period, t + 0.5 * dt);
-        void **src = bufs[(n - n_begin) & 1], **dst = bufs[(n - n_begin + 1) & 1];
-        e = launch_step(ctx, src[0], src[1], dst[0], dst[1], dt, c1, c2, c3, coltab, rowtab, s);
-        if (e == hipSuccess && ctx->inflow) e = launch_inflow(ctx, dst[0], dst[1], c1, dt, s);
-        if (e == hipSuccess && ctx->face)
-            e = launch_face(ctx, src[0], src[1], dst[0], dst[1], dt, c1, c2, c3, s);
+    const int most = multi_steps(ctx, dt);  // steps a launch may take
+    // an even number of launches ends in the caller's buffers
+    int64_t left = (n_end - n_begin + most - 1) / most;
+    if ((left & 1) && left < n_end - n_begin) left++;
+    int cur = 0;  // the buffers that hold the state
+    for (int64_t n = n_begin; n < n_end;) {
+        int64_t want = left > 1 ? (n_end - n + left - 1) / left : n_end - n;
+        if (want > most) want = most;
+        void **src = bufs[cur], **dst = bufs[cur ^ 1];
+        double c[kMultiSteps][3];
+        for (int q = 0; q < want; q++) {
+            const double t = t0 + double(n + q) * dt;
+            c[q][0] = time_factor(ctx->period, t + dt);
+            c[q][1] = time_factor(ctx->period, t);
+            c[q][2] = time_factor(ctx->period, t + 0.5 * dt);
+        }
+        int took = 0;
+        if (want > 1)
+            e = launch_multi_step(ctx, int(want), c, src[0], src[1], dst[0], dst[1], dt, coltab, rowtab,
+                                  s, &took);
+        if (e == hipSuccess && took == 0) {
+            took = 1;
+            e = launch_step(ctx, src[0], src[1], dst[0], dst[1], dt, c[0][0], c[0][1], c[0][2],
+                            coltab, rowtab, s);
+            if (e == hipSuccess && ctx->inflow) e = launch_inflow(ctx, dst[0], dst[1], c[0][0], dt, s);
+            if (e == hipSuccess && ctx->face)
+                e = launch_face(ctx, src[0], src[1], dst[0], dst[1], dt, c[0][0], c[0][1], c[0][2], s);
+        }
         if (e != hipSuccess) return e;
+        n += took;
+        left--;
+        cur ^= 1;
     }
-    if ((n_end - n_begin) & 1) {
+    if (cur) {
         // the result sits in the workspace: copy the valid part of each plane back
         const size_t es = elem_size(ctx);
         const size_t w = size_t(ctx->g.n[0]) * es, p = size_t(ctx->g.pitch) * es;

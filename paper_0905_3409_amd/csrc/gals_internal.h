@@ -221,6 +221,15 @@ void set_error_v(const char *fmt, va_list ap);
 hipError_t launch_step(const gals_ctx *ctx, const void *phi, const void *grad, void *phi_o,
                        void *grad_o, double dt, double c1, double c2, double c3,
                        const void *coltab, const void *rowtab, hipStream_t s);
+// Several steps of a small 2D grid in one launch (multi2d.hip). multi_steps: how
+// many a launch should take at step size dt (1: none). launch_multi_step takes
+// up to k <= kMultiSteps of them (time factors c[q]) and says how many in *took,
+// 0 if not even two fit (then nothing was launched).
+constexpr int kMultiSteps = 4;
+int multi_steps(const gals_ctx *ctx, double dt);
+hipError_t launch_multi_step(const gals_ctx *ctx, int k, const double (*c)[3], const void *phi,
+                             const void *grad, void *phi_o, void *grad_o, double dt,
+                             const void *coltab, const void *rowtab, hipStream_t s, int *took);
 // Per-column / per-row stream-function tables (GALS_VEL_STREAM_SIN only).
 hipError_t launch_stream_tables(const gals_ctx *ctx, void *coltab, void *rowtab, hipStream_t s);
 // sin(pi x), cos(pi x) at the node coordinates of each axis (x, then y, then

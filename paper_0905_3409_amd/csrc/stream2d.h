@@ -301,14 +301,12 @@ __device__ __forceinline__ void stream_trace(const Geom &g, const P &p, const St
 // The part of a stream-function step after the trace and the gather: the
 // bicubic, the boundary treatment of its gradient, and the update
 // (superconsistent, or Heun's method with grad v at the foot from the node's
-// jet) into the output planes.
+// jet): phi, psi_x, psi_y into out.
 template <typename T, bool TAYLOR, int PSI, class P>
-__device__ __forceinline__ void stream_finish(const Geom &g, const P &p, const Stage<T> &st,
+__device__ __forceinline__ void stream_values(const Geom &g, const P &p, const Stage<T> &st,
                                               double dt, const T *__restrict__ U,
                                               const T *__restrict__ Y, const StreamFoot<T> &f,
-                                              const T (&d)[4][4], T *__restrict__ phi_o,
-                                              T *__restrict__ gx_o, T *__restrict__ gy_o, int i,
-                                              int j)
+                                              const T (&d)[4][4], int i, int j, T *out)
 {
     Basis<T> bx, by;
     basis<T, false>(T(f.xi[0]), geo_h<T>(g, 0), geo_ih<T>(g, 0), bx);
@@ -317,23 +315,19 @@ __device__ __forceinline__ void stream_finish(const Geom &g, const P &p, const S
     hermite2d(d, bx, by, H, Hx, Hy);
     if (f.outb[0]) Hx = T(0);
     if (f.outb[1]) Hy = T(0);
-
-    const unsigned o = unsigned(j) * unsigned(g.pitch) + unsigned(i);
-    pstore(phi_o, o, H);
+    out[0] = H;
     if constexpr (PSI == GALS_PSI_HEUN) {
-        T vf[2], Af[4], ps[2];
+        T vf[2], Af[4];
         const T gH[2] = {Hx, Hy};
         stream_stage<T, TAYLOR>(p, f.jet, U, Y, g, i, j, node_coord(g.lo[0], i, g.h[0]),
                                 node_coord(g.lo[1], j, g.h[1]), T((f.s[0] - double(i)) * g.h[0]),
                                 T((f.s[1] - double(j)) * g.h[1]), vf, Af);
 #pragma unroll
         for (int k = 0; k < 4; k++) Af[k] *= st.c2;
-        heun_gradient<T, 2>(Af, f.A0, T(dt), gH, ps);
-        pstore(gx_o, o, ps[0]);
-        pstore(gy_o, o, ps[1]);
+        heun_gradient<T, 2>(Af, f.A0, T(dt), gH, out + 1);
     } else {
-        pstore(gx_o, o, f.J[0] * Hx + f.J[2] * Hy);
-        pstore(gy_o, o, f.J[1] * Hx + f.J[3] * Hy);
+        out[1] = f.J[0] * Hx + f.J[2] * Hy;
+        out[2] = f.J[1] * Hx + f.J[3] * Hy;
     }
 }
 
@@ -355,7 +349,12 @@ __device__ __forceinline__ void stream_node(const Geom &g, const P &p, const Sta
     // held in scalar registers across it
     gather2d<T, MIX>(g, plane_rsrc(phi, g.plane), plane_rsrc(gx, g.plane),
                      plane_rsrc(gy, g.plane), f.cell[0], f.cell[1], d);
-    stream_finish<T, TAYLOR, PSI>(g, p, st, dt, U, Y, f, d, phi_o, gx_o, gy_o, i, j);
+    T v[3];
+    stream_values<T, TAYLOR, PSI>(g, p, st, dt, U, Y, f, d, i, j, v);
+    const unsigned o = unsigned(j) * unsigned(g.pitch) + unsigned(i);
+    pstore(phi_o, o, v[0]);
+    pstore(gx_o, o, v[1]);
+    pstore(gy_o, o, v[2]);
 }
 
 // Workgroups are dealt to the 8 XCDs round-robin by id, and each XCD has its
