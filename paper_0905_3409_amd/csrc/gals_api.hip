@@ -106,40 +106,42 @@ bool axis_tables(const gals_ctx *ctx, int64_t steps)
     return trig && double(ctx->g.nodes) * double(steps) >= double(1 << 21);
 }
 
-// Velocity tables of the field into the workspace.
-hipError_t launch_tables(const gals_ctx *ctx, int64_t steps, void *workspace, hipStream_t s)
+// Where an advance of `steps` steps keeps the field's tables, both null if it
+// reads none.
+void table_slots(const gals_ctx *ctx, int64_t steps, void *workspace, void *&coltab, void *&rowtab)
 {
     char *ws = (char *)workspace;
-    if (axis_tables(ctx, steps))
-        return launch_axis_tables(ctx, ws + axistab_offset(ctx), s);
-    if (ctx->vel_kind != GALS_VEL_STREAM_SIN) return hipSuccess;
-    return launch_stream_tables(ctx, ws + coltab_offset(ctx), ws + rowtab_offset(ctx), s);
-}
-
-// Steps n_begin .. n_end-1 of an advance of `steps` steps from time t0 (step n
-// starts at t0 + n dt), ping-ponging through the workspace's state copy; the
-// result ends in (phi, grad). The tables (launch_tables with the same `steps`)
-// must be in the workspace already.
-hipError_t advance_core(const gals_ctx *ctx, void *phi, void *grad, double t0, double dt,
-                        int64_t n_begin, int64_t n_end, int64_t steps, void *workspace,
-                        hipStream_t s)
-{
-    const size_t pb = size_t(ctx->g.plane) * elem_size(ctx);
-    char *ws = (char *)workspace;
-    void *bufs[2][2] = {{phi, grad}, {ws, ws + pb}};
-    void *coltab = nullptr, *rowtab = nullptr;
+    coltab = rowtab = nullptr;
     if (ctx->vel_kind == GALS_VEL_STREAM_SIN) {
         coltab = ws + coltab_offset(ctx);
         rowtab = ws + rowtab_offset(ctx);
     } else if (axis_tables(ctx, steps)) {
-        coltab = ws + axistab_offset(ctx);  // the per-axis sin/cos table
+        coltab = ws + axistab_offset(ctx);
     }
-    hipError_t e = hipSuccess;
+}
+
+// Steps n_begin .. n_end-1 of an advance of `steps` steps from time t0 (step n
+// starts at t0 + n dt), ping-ponging through the workspace's state copy; the
+// result ends in (phi, grad). Builds the field's tables first if `tables`, else
+// they must be in the workspace already.
+hipError_t advance_core(const gals_ctx *ctx, void *phi, void *grad, double t0, double dt,
+                        int64_t n_begin, int64_t n_end, int64_t steps, bool tables,
+                        void *workspace, hipStream_t s)
+{
+    const size_t pb = size_t(ctx->g.plane) * elem_size(ctx);
+    char *ws = (char *)workspace;
+    void *bufs[2][2] = {{phi, grad}, {ws, ws + pb}};
+    void *coltab, *rowtab;
+    table_slots(ctx, steps, workspace, coltab, rowtab);
     const int most = multi_steps(ctx, dt);  // steps a launch may take
-    // an even number of launches ends in the caller's buffers
+    // an even number of launches from the caller's buffers, or an odd one from
+    // the workspace's copy, ends in the caller's buffers
     int64_t left = (n_end - n_begin + most - 1) / most;
     if ((left & 1) && left < n_end - n_begin) left++;
-    int cur = 0;  // the buffers that hold the state
+    int cur = int(left & 1);  // the buffers that hold the state
+    hipError_t e = launch_prepare(ctx, tables ? coltab : nullptr, rowtab, phi, grad,
+                                  cur ? ws : nullptr, s);
+    if (e != hipSuccess) return e;
     for (int64_t n = n_begin; n < n_end;) {
         int64_t want = left > 1 ? (n_end - n + left - 1) / left : n_end - n;
         if (want > most) want = most;
@@ -169,7 +171,8 @@ hipError_t advance_core(const gals_ctx *ctx, void *phi, void *grad, double t0, d
         cur ^= 1;
     }
     if (cur) {
-        // the result sits in the workspace: copy the valid part of each plane back
+        // a launch took fewer steps than planned and the result sits in the
+        // workspace: copy the valid part of each plane back
         const size_t es = elem_size(ctx);
         const size_t w = size_t(ctx->g.n[0]) * es, p = size_t(ctx->g.pitch) * es;
         const size_t rows = size_t(ctx->g.n[1]) * size_t(ctx->g.n[2]);
@@ -479,8 +482,7 @@ int gals_advance(gals_ctx *ctx, void *phi, void *grad, double t0, double dt, int
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "gals_advance: pending HIP error");
     hipStream_t s = (hipStream_t)stream;
-    e = launch_tables(ctx, steps, workspace, s);
-    if (e == hipSuccess) e = advance_core(ctx, phi, grad, t0, dt, 0, steps, steps, workspace, s);
+    e = advance_core(ctx, phi, grad, t0, dt, 0, steps, steps, true, workspace, s);
     return e == hipSuccess ? GALS_OK : hip_fail(e, "gals_advance: launch");
 }
 
@@ -514,8 +516,7 @@ int gals_advance_noalloc(gals_ctx *ctx, void *phi, void *grad, double t0, double
     e = scratch_address(ctx->device, &ws);
     if (e != hipSuccess) return hip_fail(e, "gals_advance_noalloc: hipGetSymbolAddress");
     hipStream_t s = (hipStream_t)stream;
-    e = launch_tables(ctx, steps, ws, s);
-    if (e == hipSuccess) e = advance_core(ctx, phi, grad, t0, dt, 0, steps, steps, ws, s);
+    e = advance_core(ctx, phi, grad, t0, dt, 0, steps, steps, true, ws, s);
     return e == hipSuccess ? GALS_OK : hip_fail(e, "gals_advance_noalloc: launch");
 }
 
@@ -706,12 +707,12 @@ int gals_advance_save(gals_ctx *ctx, void *phi, void *grad, double t0, double dt
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "gals_advance_save: pending HIP error");
     hipStream_t s = (hipStream_t)stream;
-    e = launch_tables(ctx, steps, workspace, s);
     for (int64_t k = 0; k < nsegments(steps, every) && e == hipSuccess; k++) {
         char *slot = (char *)ckpt + size_t(k) * seg_state_bytes(ctx);
         e = copy_state(ctx, slot, slot + pb, phi, grad, s);
         const int64_t n0 = k * every, n1 = n0 + every < steps ? n0 + every : steps;
-        if (e == hipSuccess) e = advance_core(ctx, phi, grad, t0, dt, n0, n1, steps, workspace, s);
+        if (e == hipSuccess)
+            e = advance_core(ctx, phi, grad, t0, dt, n0, n1, steps, k == 0, workspace, s);
     }
     return e == hipSuccess ? GALS_OK : hip_fail(e, "gals_advance_save: launch");
 }
@@ -756,7 +757,7 @@ int gals_adjoint(gals_ctx *ctx, const void *ckpt, size_t ckpt_bytes, double t0, 
     double *part = (double *)(ws + adj_part_offset(ctx, every));
     const int nblocks = int(adjoint_blocks(ctx));
     void *coltab = ws + coltab_offset(ctx), *rowtab = ws + rowtab_offset(ctx);
-    e = launch_tables(ctx, 1, workspace, s);
+    e = launch_prepare(ctx, coltab, rowtab, nullptr, nullptr, nullptr, s);
     if (e == hipSuccess) e = launch_zero(part, int64_t(nblocks) * 16, s);
     if (e == hipSuccess) e = launch_zero(dS, 16, s);
     // each adjoint step zeroes the buffer it reads, which then receives the
@@ -826,14 +827,14 @@ int gals_adjoint_step(gals_ctx *ctx, const void *phi, const void *grad, double t
     char *ws = (char *)workspace;
     double *part = (double *)(ws + adj_part_offset(ctx, 1));
     const int nblocks = int(adjoint_blocks(ctx));
-    e = launch_tables(ctx, 1, workspace, s);
+    void *coltab = ws + coltab_offset(ctx), *rowtab = ws + rowtab_offset(ctx);
+    e = launch_prepare(ctx, coltab, rowtab, nullptr, nullptr, nullptr, s);
     if (e == hipSuccess) e = launch_zero(part, int64_t(nblocks) * 16, s);
     if (e == hipSuccess) e = launch_zero(lam_out, 3 * ctx->g.plane, s);
     if (e == hipSuccess)
         e = launch_adjoint_step(ctx, phi, grad, const_cast<double *>(lam_in), lam_out, false, part, dt,
                                 time_factor(ctx->period, t + dt), time_factor(ctx->period, t),
-                                time_factor(ctx->period, t + 0.5 * dt), ws + coltab_offset(ctx),
-                                ws + rowtab_offset(ctx), s);
+                                time_factor(ctx->period, t + 0.5 * dt), coltab, rowtab, s);
     if (e == hipSuccess) e = launch_fold_grad(part, nblocks, dS, s);
     return e == hipSuccess ? GALS_OK : hip_fail(e, "gals_adjoint_step: launch");
 }

@@ -401,7 +401,7 @@ int gals_batch_create(gals_batch **out, int64_t nprob, const int64_t *ncell, con
         offs += 3 * g.plane;  // planes are multiples of 64 elements: alignment kept
         b->tab[p] = tabs;
         tabs += round_up(int64_t(g.n[0] + g.n[1]) * kJet, 64);
-        const int entries = g.n[0] + g.n[1];
+        const int entries = int(stream_table_threads(g));  // at most 2^23 + 8
         if (entries > b->max_entries) b->max_entries = entries;
     }
     b->total_elems = offs;

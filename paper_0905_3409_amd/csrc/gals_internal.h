@@ -90,6 +90,9 @@ inline void geom_finish(Geom &g)
         g.n_magic[a] = g.n[a] > 1 ? unsigned((uint64_t(1) << 32) / unsigned(g.n[a])) : 0xFFFFFFFFu;
 }
 
+// Threads that build a grid's stream-function tables (stream_table_entry).
+inline int64_t stream_table_threads(const Geom &g) { return 4 * (int64_t(g.n[0]) + g.n[1]); }
+
 // h, 1/h and 1/(2h) of axis a in the working precision T.
 template <typename T>
 __device__ __forceinline__ T geo_h(const Geom &g, int a)
@@ -230,11 +233,13 @@ int multi_steps(const gals_ctx *ctx, double dt);
 hipError_t launch_multi_step(const gals_ctx *ctx, int k, const double (*c)[3], const void *phi,
                              const void *grad, void *phi_o, void *grad_o, double dt,
                              const void *coltab, const void *rowtab, hipStream_t s, int *took);
-// Per-column / per-row stream-function tables (GALS_VEL_STREAM_SIN only).
-hipError_t launch_stream_tables(const gals_ctx *ctx, void *coltab, void *rowtab, hipStream_t s);
-// sin(pi x), cos(pi x) at the node coordinates of each axis (x, then y, then
-// z; one pair per node) for 3D sine vector potentials (kernels_step.hip).
-hipError_t launch_axis_tables(const gals_ctx *ctx, void *tab, hipStream_t s);
+// One launch before the first step (kernels_step.hip): the field's tables into
+// coltab and rowtab (per-column / per-row stream-function tables; for trig
+// fields and vector potentials sin(pi x), cos(pi x) per node of each axis, x,
+// then y, then z, into coltab; none if coltab is NULL), and the state's copy
+// (1 + dim planes) into `copy` unless that is NULL.
+hipError_t launch_prepare(const gals_ctx *ctx, void *coltab, void *rowtab, const void *phi,
+                          const void *grad, void *copy, hipStream_t s);
 
 // Inflow boundary conditions after a step of size dt (boundary.hip):
 // Dirichlet data at time factor c, and homogeneous Neumann inflow by the face

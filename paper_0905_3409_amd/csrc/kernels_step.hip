@@ -401,19 +401,6 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
 // evaluating sin and cos at the stage points. The mode sums are those of
 // vel_vecpot.
 // ---------------------------------------------------------------------------
-template <typename T>
-__global__ __launch_bounds__(kBlock) void k_axis_tables(Geom g, T *__restrict__ tab)
-{
-    const int id = int(blockIdx.x) * kBlock + int(threadIdx.x);
-    int r = id, a = 0;
-    while (a < 3 && r >= g.n[a]) r -= g.n[a++];
-    if (a >= 3) return;
-    double s, c;
-    sincospi(node_coord(g.lo[a], r, g.h[a]), &s, &c);
-    tab[2 * id] = T(s);
-    tab[2 * id + 1] = T(c);
-}
-
 // Velocity at one stage point from the multiples of each axis: through LDS
 // (LDS, the FP32 kernel) or by per-lane selects.
 template <typename T, bool LDS>
@@ -532,16 +519,95 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
 }
 
 // ---------------------------------------------------------------------------
-// Sine stream-function fields (see stream2d.h).
+// What an advance needs before its first step, in one launch: the field's tables
+// (TAB), and, when an odd number of launches follows, the state's copy in the
+// workspace that the first of them reads, so that the last one ends in the
+// caller's buffers. The first `tab_blocks` blocks build entries, the others copy
+// whole planes, padding included (the copy's padding is never read), 16 bytes a
+// thread at a time where the caller's planes allow. (A table launch before and
+// one pitched copy per plane after the last step: 24 us per one-step call on 501 x
+// 380 FP32 nodes, 81 on 2049^2, 303 on 4097 x 4096; 17, 62 and 244 with this.)
 // ---------------------------------------------------------------------------
-template <typename T>
-__global__ __launch_bounds__(kBlock) void k_stream_tables(Geom g, Vel<double> p,
-                                                          T *__restrict__ coltab,
-                                                          T *__restrict__ rowtab)
+enum { kTabNone = 0, kTabStream = 1, kTabAxis = 2 };
+
+template <typename V>
+__device__ __forceinline__ void copy_span(const void *__restrict__ src, void *__restrict__ dst,
+                                          int64_t bytes, int64_t id, int64_t stride)
 {
-    stream_table_entry(g, p.S, int(blockIdx.x) * kBlock + int(threadIdx.x), coltab, rowtab);
+    const V *s = static_cast<const V *>(src);
+    V *d = static_cast<V *>(dst);
+    for (int64_t k = id; k < bytes / int64_t(sizeof(V)); k += stride) d[k] = s[k];
 }
 
+template <typename T, int TAB>
+__global__ __launch_bounds__(kBlock) void k_prepare(Geom g, Vel<double> p, unsigned tab_blocks,
+                                                    T *__restrict__ tab0, T *__restrict__ tab1,
+                                                    const T *__restrict__ phi,
+                                                    const T *__restrict__ grad,
+                                                    T *__restrict__ copy, int wide)
+{
+    if (blockIdx.x < tab_blocks) {
+        const int id = int(blockIdx.x) * kBlock + int(threadIdx.x);
+        if constexpr (TAB == kTabStream) {
+            stream_table_entry(g, p.S, id, tab0, tab1);
+        } else if constexpr (TAB == kTabAxis) {
+            int r = id, a = 0;
+            while (a < 3 && r >= g.n[a]) r -= g.n[a++];
+            if (a >= 3) return;
+            double s, c;
+            sincospi(node_coord(g.lo[a], r, g.h[a]), &s, &c);
+            tab0[2 * id] = T(s);
+            tab0[2 * id + 1] = T(c);
+        }
+        return;
+    }
+    const int64_t id = int64_t(blockIdx.x - tab_blocks) * kBlock + threadIdx.x;
+    const int64_t stride = int64_t(gridDim.x - tab_blocks) * kBlock;
+    const int64_t pb = g.plane * int64_t(sizeof(T));  // a multiple of 256 bytes
+    if (wide) {
+        copy_span<uint4>(phi, copy, pb, id, stride);
+        copy_span<uint4>(grad, copy + g.plane, pb * g.dim, id, stride);
+    } else {
+        copy_span<T>(phi, copy, pb, id, stride);
+        copy_span<T>(grad, copy + g.plane, pb * g.dim, id, stride);
+    }
+}
+
+template <typename T>
+static hipError_t prepare_typed(const gals_ctx *ctx, int tab, void *tab0, void *tab1,
+                                const void *phi, const void *grad, void *copy, hipStream_t s)
+{
+    const Geom &g = ctx->g;
+    const int64_t entries = tab == kTabStream ? stream_table_threads(g)
+                            : tab == kTabAxis ? int64_t(g.n[0]) + g.n[1] + g.n[2] : 0;
+    const unsigned tb = unsigned((entries + kBlock - 1) / kBlock);
+    const bool wide = (uintptr_t(phi) | uintptr_t(grad)) % 16 == 0;
+    int64_t cb = 0;
+    if (copy) {
+        const int64_t spans = g.plane * (1 + g.dim) * int64_t(sizeof(T)) / 16;
+        cb = (spans + kBlock - 1) / kBlock;
+        if (cb > 8192) cb = 8192;
+    }
+    if (tb + cb == 0) return hipSuccess;
+    auto kern = tab == kTabStream ? k_prepare<T, kTabStream>
+                : tab == kTabAxis ? k_prepare<T, kTabAxis> : k_prepare<T, kTabNone>;
+    hipLaunchKernelGGL(kern, dim3(tb + unsigned(cb)), dim3(kBlock), 0, s, g, ctx->vd, tb, (T *)tab0,
+                       (T *)tab1, (const T *)phi, (const T *)grad, (T *)copy, int(wide));
+    return hipGetLastError();
+}
+
+hipError_t launch_prepare(const gals_ctx *ctx, void *coltab, void *rowtab, const void *phi,
+                          const void *grad, void *copy, hipStream_t s)
+{
+    const int tab = !coltab ? kTabNone : ctx->vel_kind == GALS_VEL_STREAM_SIN ? kTabStream : kTabAxis;
+    return ctx->prec == GALS_F32
+               ? prepare_typed<float>(ctx, tab, coltab, rowtab, phi, grad, copy, s)
+               : prepare_typed<double>(ctx, tab, coltab, rowtab, phi, grad, copy, s);
+}
+
+// ---------------------------------------------------------------------------
+// Sine stream-function fields (see stream2d.h).
+// ---------------------------------------------------------------------------
 // GA-CIR step for the sine stream-function field. Launch: blocks of 64 x 4
 // threads over 64 x 4 node tiles; each wave owns 64 consecutive nodes of one
 // row, so the row table is read once per wave through scalar loads. The cell
@@ -566,18 +632,6 @@ __global__ __launch_bounds__(kBlock) void k_step2d_stream(
                                      phi_o, grad_o, grad_o + g.plane, i, j);
 }
 
-hipError_t launch_stream_tables(const gals_ctx *ctx, void *coltab, void *rowtab, hipStream_t s)
-{
-    const unsigned blocks = unsigned((ctx->g.n[0] + ctx->g.n[1] + kBlock - 1) / kBlock);
-    if (ctx->prec == GALS_F32)
-        hipLaunchKernelGGL(k_stream_tables<float>, dim3(blocks), dim3(kBlock), 0, s, ctx->g,
-                           ctx->vd, (float *)coltab, (float *)rowtab);
-    else
-        hipLaunchKernelGGL(k_stream_tables<double>, dim3(blocks), dim3(kBlock), 0, s, ctx->g,
-                           ctx->vd, (double *)coltab, (double *)rowtab);
-    return hipGetLastError();
-}
-
 template <typename T, int MIX, int PSI>
 static hipError_t launch_stream(const gals_ctx *ctx, const Vel<T> &p, const void *phi,
                                 const void *grad, void *phi_o, void *grad_o, double dt,
@@ -590,19 +644,6 @@ static hipError_t launch_stream(const gals_ctx *ctx, const Vel<T> &p, const void
     hipLaunchKernelGGL((k_step2d_stream<T, MIX, sizeof(T) == 4, PSI>), grid, dim3(64, 4), 0, s,
                        ctx->g, p, st, dt, (const T *)coltab, (const T *)rowtab, (const T *)phi,
                        (const T *)grad, (T *)phi_o, (T *)grad_o);
-    return hipGetLastError();
-}
-
-hipError_t launch_axis_tables(const gals_ctx *ctx, void *tab, hipStream_t s)
-{
-    const int count = ctx->g.n[0] + ctx->g.n[1] + ctx->g.n[2];
-    const unsigned blocks = unsigned((count + kBlock - 1) / kBlock);
-    if (ctx->prec == GALS_F32)
-        hipLaunchKernelGGL(k_axis_tables<float>, dim3(blocks), dim3(kBlock), 0, s, ctx->g,
-                           (float *)tab);
-    else
-        hipLaunchKernelGGL(k_axis_tables<double>, dim3(blocks), dim3(kBlock), 0, s, ctx->g,
-                           (double *)tab);
     return hipGetLastError();
 }
 

@@ -146,7 +146,8 @@ __device__ __forceinline__ void multi_node(const Geom &g, const StreamSteps<T> &
     T d[4][4];
     const T *t = buf + 3 * ((ft.cell[1] - R.y0) * w + (ft.cell[0] - R.x0));
     gather2d_lds<T, MIX>(g, t, t + 3 * w, ft.cell[0], d);
-    stream_values<T, sizeof(T) == 4, PSI>(g, f, st, dt, U, Y, ft, d, i, j, out);
+    stream_values<T, sizeof(T) == 4, PSI>(g, f, st, dt, U, Y, ft, d, i, j,
+                                          [&](int q, T v) { out[q] = v; });
 }
 
 template <typename T, class F, int MIX, int PSI>
