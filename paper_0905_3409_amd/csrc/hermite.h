@@ -640,7 +640,11 @@ __device__ __forceinline__ void hermite3d_full(const T d[8][8], const Basis<T> &
 // 192 multiply-adds, the differences with their one-sided forms and selects
 // (240 instructions a node) gone. phi enters as its differences from the
 // cell's first vertex: its derivatives are divided differences, and rounding
-// then acts on values of the size of h |grad phi| instead of |phi|.
+// then acts on values of the size of h |grad phi| instead of |phi|. With the
+// Hessian (SECOND) the whole linear part at that vertex is taken out of the data
+// and added back: second differences of the gradient would leave u |grad phi| / h
+// (error of the FP32 curvature on 257^3 nodes 1.5e-5 with neither, 8e-6 with the
+// first, 2.9e-6 with both).
 //
 // Bound: vector issue (FP64 and the vector potential), the L1's rate for 64
 // scattered loads a node where the trace is cheap. Measured against forming
@@ -748,7 +752,8 @@ __device__ __forceinline__ void tricubic_central(const Geom &g, Rsrc rphi, Rsrc 
         T a00, a10, a01, a20, a11, a02;
     };
     Acc A[2] = {};
-    T ref = T(0);
+    T ref = T(0), p0 = T(0), p1 = T(0), p2 = T(0);  // phi and its gradient at the first vertex
+    const T gh[3] = {geo_h<T>(g, 0), geo_h<T>(g, 1), geo_h<T>(g, 2)};
     auto dot = [](const T *u, const T *w) { return u[0] * w[0] + u[1] * w[1] + u[2] * w[2] + u[3] * w[3]; };
     auto sums = [&](Acc &a, bool first, T x0, T x1, T x2, T wy, T dwy, T ddwy) {
         a.a00 = first ? x0 * wy : a.a00 + x0 * wy;
@@ -760,28 +765,43 @@ __device__ __forceinline__ void tricubic_central(const Geom &g, Rsrc rphi, Rsrc 
             a.a20 = first ? x2 * wy : a.a20 + x2 * wy;
         }
     };
-    auto add = [&](Acc &a, bool first, const T *w, T wy, T dwy, T ddwy) {
-        const T u[4] = {w[0], w[1], w[2], xedge ? T(0) : w[3]};
+    auto add = [&](Acc &a, bool first, const T *w, T base, T wy, T dwy, T ddwy) {
+        const T u[4] = {w[0] - base, w[1] - base, w[2] - base, xedge ? T(0) : w[3] - base};
         sums(a, first, dot(u, sx.w), dot(u, sx.dw), SECOND ? dot(u, sx.ddw) : T(0), wy, dwy, ddwy);
     };
     auto sum = [&](int q, const T *u) {
-        const int part = q & 3;
+        const int part = q & 3, vz = q >> 2;
         if (part < 2) {
+            if (SECOND && q == 0) p2 = xlo ? u[4] : u[5];
 #pragma unroll
             for (int r = 0; r < 2; r++) {
                 const int jy = 2 * part + r;
-                add(A[1], jy == 0, u + 4 * r, sy.w[jy], sy.dw[jy], SECOND ? sy.ddw[jy] : T(0));
+                add(A[1], jy == 0, u + 4 * r, p2, sy.w[jy], sy.dw[jy], SECOND ? sy.ddw[jy] : T(0));
             }
         } else {
             const int vy = part - 2;
-            if (q == 2) ref = u[4];
-            const T du = u[5] - u[4], r = u[4] - ref;  // phi along x, and above ref
-            const T x0 = r + du * bx.w[1] + u[6] * bx.w[2] + u[7] * bx.w[3];
-            const T x1 = du * bx.dw[1] + u[6] * bx.dw[2] + u[7] * bx.dw[3];
+            if (q == 2) {
+                ref = u[4];
+                if constexpr (SECOND) {
+                    p0 = u[6];
+                    p1 = xlo ? u[0] : u[1];
+                }
+            }
+            T du = u[5] - u[4], r = u[4] - ref;  // phi along x, and above ref
+            T g0 = u[6], g1 = u[7];
+            if constexpr (SECOND) {
+                du -= p0 * gh[0];
+                if (vy) r -= p1 * gh[1];
+                if (vz) r -= p2 * gh[2];
+                g0 -= p0;
+                g1 -= p0;
+            }
+            const T x0 = r + du * bx.w[1] + g0 * bx.w[2] + g1 * bx.w[3];
+            const T x1 = du * bx.dw[1] + g0 * bx.dw[2] + g1 * bx.dw[3];
             T x2 = T(0);
-            if constexpr (SECOND) x2 = du * bx.ddw[1] + u[6] * bx.ddw[2] + u[7] * bx.ddw[3];
+            if constexpr (SECOND) x2 = du * bx.ddw[1] + g0 * bx.ddw[2] + g1 * bx.ddw[3];
             sums(A[0], vy == 0, x0, x1, x2, by.w[vy], by.dw[vy], SECOND ? by.ddw[vy] : T(0));
-            add(A[0], false, u, by.w[2 + vy], by.dw[2 + vy], SECOND ? by.ddw[2 + vy] : T(0));
+            add(A[0], false, u, p1, by.w[2 + vy], by.dw[2 + vy], SECOND ? by.ddw[2 + vy] : T(0));
         }
     };
     T h = 0, hx = 0, hy = 0, hz = 0;
@@ -811,19 +831,26 @@ __device__ __forceinline__ void tricubic_central(const Geom &g, Rsrc rphi, Rsrc 
         sum(q, u[q & 1]);
         asm volatile("" : "+v"(A[0].a00), "+v"(A[0].a10), "+v"(A[0].a01), "+v"(A[1].a00),
                      "+v"(A[1].a10), "+v"(A[1].a01));
+        if constexpr (SECOND)
+            asm volatile("" : "+v"(A[0].a20), "+v"(A[0].a11), "+v"(A[0].a02), "+v"(A[1].a20),
+                         "+v"(A[1].a11), "+v"(A[1].a02));
         if ((q & 3) == 3) {
             reduce(A[0], q >> 2);
             reduce(A[1], 2 + (q >> 2));
         }
         __builtin_amdgcn_sched_barrier(0);
     }
-    H = ref + h;
-    G[0] = hx; G[1] = hy; G[2] = hz;
     if constexpr (SECOND) {
+        h += p0 * (xi[0] * gh[0]) + p1 * (xi[1] * gh[1]) + p2 * (xi[2] * gh[2]);
+        hx += p0;
+        hy += p1;
+        hz += p2;
         Hs[0] = hxx; Hs[1] = hxy; Hs[2] = hxz;
         Hs[3] = hxy; Hs[4] = hyy; Hs[5] = hyz;
         Hs[6] = hxz; Hs[7] = hyz; Hs[8] = hzz;
     }
+    H = ref + h;
+    G[0] = hx; G[1] = hy; G[2] = hz;
 }
 
 // Value and gradient of the tricubic of cell c at local coordinates xi, for
