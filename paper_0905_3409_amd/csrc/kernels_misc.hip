@@ -116,18 +116,24 @@ hipError_t launch_eval(const gals_ctx *ctx, const void *phi, const void *grad, c
 #undef GALS_EVAL
 }
 
-__device__ __forceinline__ int64_t node_offset(const Geom &g, int64_t id)
+// Offset of node id in a plane: 32-bit, by the row length's magic number (the
+// host keeps nodes below 2^31 and planes below 2 GiB; rows of 3D planes are
+// contiguous in (j, k)).
+__device__ __forceinline__ unsigned node_offset(const Geom &g, unsigned id)
 {
-    const int64_t i = id % g.n[0];
-    const int64_t r = id / g.n[0];
-    return r * g.pitch + i;  // rows of 3D planes are contiguous in (j, k)
+    unsigned i;
+    const unsigned r = udiv_magic(id, unsigned(g.n[0]), g.n_magic[0], i);
+    return r * unsigned(g.pitch) + i;
 }
 
 // slots: 0 max|dphi| 1 max|dpsi| 2 sum|dH| 3 max band 4 sum H(-phi)
 //        5 sum H(-phi_ref) 6 nonfinite count 7 max|phi_ref|
 constexpr unsigned kNormsMax = (1u << 0) | (1u << 1) | (1u << 3) | (1u << 7);
 
-template <typename T>
+// Two nodes a pass, their loads issued together; per thread the nodes are summed
+// in the order of their ids. Bound: the two states' bytes. 2049^2 FP32 (100 MB):
+// 32 us with 64-bit divisions and one node a pass, 23 with this.
+template <typename T, int D>
 __global__ __launch_bounds__(kBlock) void k_norms(Geom g, const T *__restrict__ phi,
                                                   const T *__restrict__ grad,
                                                   const T *__restrict__ phr,
@@ -135,16 +141,16 @@ __global__ __launch_bounds__(kBlock) void k_norms(Geom g, const T *__restrict__ 
                                                   double band, double *__restrict__ partials)
 {
     double acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    const int64_t stride = int64_t(gridDim.x) * kBlock;
-    for (int64_t id = int64_t(blockIdx.x) * kBlock + threadIdx.x; id < g.nodes; id += stride) {
-        const int64_t o = node_offset(g, id);
-        const double p = double(phi[o]), r = double(phr[o]);
+    const unsigned stride = gridDim.x * unsigned(kBlock), nodes = unsigned(g.nodes);
+    auto add = [&](const T *u, const T *w) {
+        const double p = double(u[0]), r = double(w[0]);
         const double e = fabs(p - r);
         acc[0] = fmax(acc[0], e);
         double nf = isfinite(p) ? 0.0 : 1.0;
-        for (int a = 0; a < g.dim; a++) {
-            const double q = double(grad[a * g.plane + o]);
-            acc[1] = fmax(acc[1], fabs(q - double(grr[a * g.plane + o])));
+#pragma unroll
+        for (int a = 0; a < D; a++) {
+            const double q = double(u[1 + a]);
+            acc[1] = fmax(acc[1], fabs(q - double(w[1 + a])));
             nf += isfinite(q) ? 0.0 : 1.0;
         }
         acc[2] += fabs(heaviside_eps(p, eps) - heaviside_eps(r, eps));
@@ -153,6 +159,28 @@ __global__ __launch_bounds__(kBlock) void k_norms(Geom g, const T *__restrict__ 
         acc[5] += heaviside_eps(-r, eps);
         acc[6] += nf;
         acc[7] = fmax(acc[7], fabs(r));
+    };
+    auto load = [&](unsigned id, T *u, T *w) {
+        const unsigned o = node_offset(g, id);
+        u[0] = phi[o];
+        w[0] = phr[o];
+#pragma unroll
+        for (int a = 0; a < D; a++) {
+            u[1 + a] = grad[a * g.plane + o];
+            w[1 + a] = grr[a * g.plane + o];
+        }
+    };
+    // nodes and stride are below 2^31 and 2^19: id + 2 stride does not wrap
+    for (unsigned id = blockIdx.x * unsigned(kBlock) + threadIdx.x; id < nodes; id += 2 * stride) {
+        T u[2][1 + D], w[2][1 + D];
+        load(id, u[0], w[0]);
+        if (id + stride < nodes) {
+            load(id + stride, u[1], w[1]);
+            add(u[0], w[0]);
+            add(u[1], w[1]);
+        } else {
+            add(u[0], w[0]);
+        }
     }
     block_reduce<8>(acc, kNormsMax, partials + int64_t(blockIdx.x) * kRedSlots);
 }
@@ -161,14 +189,18 @@ hipError_t launch_norms(const gals_ctx *ctx, const void *phi, const void *grad,
                         const void *phi_ref, const void *grad_ref, double eps, double band,
                         double *partials, double *out, hipStream_t s)
 {
-    if (ctx->prec == GALS_F32)
-        hipLaunchKernelGGL(k_norms<float>, dim3(kRedBlocks), dim3(kBlock), 0, s, ctx->g,
-                           (const float *)phi, (const float *)grad, (const float *)phi_ref,
-                           (const float *)grad_ref, eps, band, partials);
-    else
-        hipLaunchKernelGGL(k_norms<double>, dim3(kRedBlocks), dim3(kBlock), 0, s, ctx->g,
-                           (const double *)phi, (const double *)grad, (const double *)phi_ref,
-                           (const double *)grad_ref, eps, band, partials);
+#define GALS_NORMS(T, D)                                                                           \
+    hipLaunchKernelGGL((k_norms<T, D>), dim3(kRedBlocks), dim3(kBlock), 0, s, ctx->g,              \
+                       (const T *)phi, (const T *)grad, (const T *)phi_ref, (const T *)grad_ref,   \
+                       eps, band, partials)
+    if (ctx->prec == GALS_F32) {
+        if (ctx->dim == 2) GALS_NORMS(float, 2);
+        else GALS_NORMS(float, 3);
+    } else {
+        if (ctx->dim == 2) GALS_NORMS(double, 2);
+        else GALS_NORMS(double, 3);
+    }
+#undef GALS_NORMS
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_fold<8>, dim3(1), dim3(kBlock), 0, s, partials, kRedBlocks, kNormsMax,
@@ -176,29 +208,93 @@ hipError_t launch_norms(const gals_ctx *ctx, const void *phi, const void *grad,
     return hipGetLastError();
 }
 
-// max over nodes of |v(x_node, t)|, c = c(t)
+// max over nodes of |v(x_node, t)|, c = c(t). The square root is monotone, so
+// it is taken once, of the largest square.
+template <typename T, int D>
+__device__ __forceinline__ double speed2(const T *v)
+{
+    double s = 0.0;
+#pragma unroll
+    for (int a = 0; a < D; a++) s += double(v[a]) * double(v[a]);
+    return s;
+}
+
 template <typename T, int D, int KIND>
 __global__ __launch_bounds__(kBlock) void k_max_speed(Geom g, Vel<T> p, T c,
                                                       double *__restrict__ partials)
 {
     double acc[1] = {0.0};
-    const int64_t stride = int64_t(gridDim.x) * kBlock;
-    for (int64_t id = int64_t(blockIdx.x) * kBlock + threadIdx.x; id < g.nodes; id += stride) {
-        int64_t r = id;
+    const unsigned stride = gridDim.x * unsigned(kBlock), nodes = unsigned(g.nodes);
+    for (unsigned id = blockIdx.x * unsigned(kBlock) + threadIdx.x; id < nodes; id += stride) {
+        unsigned idx[3], r = udiv_magic(id, unsigned(g.n[0]), g.n_magic[0], idx[0]);
+        if constexpr (D == 3) idx[2] = udiv_magic(r, unsigned(g.n[1]), g.n_magic[1], idx[1]);
+        else idx[1] = r;
         double x[D];
 #pragma unroll
-        for (int a = 0; a < D; a++) {
-            const int64_t ia = r % g.n[a];
-            r /= g.n[a];
-            x[a] = node_coord(g.lo[a], ia, g.h[a]);
-        }
+        for (int a = 0; a < D; a++) x[a] = node_coord(g.lo[a], idx[a], g.h[a]);
         T v[D], J[D * D];
         velocity<T, D, KIND>(p, x, c, v, J);
-        double s = 0.0;
-#pragma unroll
-        for (int a = 0; a < D; a++) s += double(v[a]) * double(v[a]);
-        acc[0] = fmax(acc[0], sqrt(s));
+        acc[0] = fmax(acc[0], speed2<T, D>(v));
     }
+    acc[0] = sqrt(acc[0]);
+    block_reduce<1>(acc, 1u, partials + int64_t(blockIdx.x) * kRedSlots);
+}
+
+// The same for a sine stream function, in tiles of kBlock columns x kSpeedRows
+// rows: a thread keeps its column's sines and cosines, the block the tile's row
+// sums P_m = sum_n S sin(n pi y), Q_m = sum_n S (n pi) cos(n pi y) in LDS, and a
+// node is eight multiply-adds, those of stream_modes in its order. 2049^2 FP32:
+// 26 us with both sines and the row sums at every node, 7 with this.
+constexpr int kSpeedRows = 32;
+
+template <typename T>
+__global__ __launch_bounds__(kBlock) void k_max_speed_stream(Geom g, Vel<T> p, T c,
+                                                             double *__restrict__ partials)
+{
+    __shared__ T rows[kSpeedRows][8];  // P_m, Q_m
+    double acc[1] = {0.0};
+    const unsigned tx = (unsigned(g.n[0]) + kBlock - 1) / kBlock;
+    const unsigned ty = (unsigned(g.n[1]) + kSpeedRows - 1) / kSpeedRows;
+    for (uint64_t t = blockIdx.x; t < uint64_t(tx) * ty; t += gridDim.x) {
+        const int i = int(t % tx) * kBlock + int(threadIdx.x), j0 = int(t / tx) * kSpeedRows;
+        const int nrows = g.n[1] - j0 < kSpeedRows ? g.n[1] - j0 : kSpeedRows;
+        __syncthreads();  // the previous tile's rows are read
+        if (int(threadIdx.x) < nrows) {
+            T sy[4], cy[4], qy[4];
+            sincos_multiples(T(node_coord(g.lo[1], j0 + int(threadIdx.x), g.h[1])), sy, cy);
+#pragma unroll
+            for (int n = 0; n < 4; n++) qy[n] = T((n + 1) * kPi) * cy[n];
+#pragma unroll
+            for (int m = 0; m < 4; m++) {
+                T P = 0, Q = 0;
+#pragma unroll
+                for (int n = 0; n < 4; n++) {
+                    P += p.S[m][n] * sy[n];
+                    Q += p.S[m][n] * qy[n];
+                }
+                rows[threadIdx.x][m] = P;
+                rows[threadIdx.x][4 + m] = Q;
+            }
+        }
+        __syncthreads();
+        if (i < g.n[0]) {
+            T sx[4], cx[4], kc[4];
+            sincos_multiples(T(node_coord(g.lo[0], i, g.h[0])), sx, cx);
+#pragma unroll
+            for (int m = 0; m < 4; m++) kc[m] = T((m + 1) * kPi) * cx[m];
+            for (int r = 0; r < nrows; r++) {
+                T fx = 0, fy = 0;
+#pragma unroll
+                for (int m = 0; m < 4; m++) {
+                    fx += kc[m] * rows[r][m];
+                    fy += sx[m] * rows[r][4 + m];
+                }
+                const T v[2] = {-c * fy, c * fx};
+                acc[0] = fmax(acc[0], speed2<T, 2>(v));
+            }
+        }
+    }
+    acc[0] = sqrt(acc[0]);
     block_reduce<1>(acc, 1u, partials + int64_t(blockIdx.x) * kRedSlots);
 }
 
@@ -213,7 +309,7 @@ static hipError_t max_speed_typed(const gals_ctx *ctx, const Vel<T> &p, double c
         hipLaunchKernelGGL((k_max_speed<T, 2, GALS_VEL_AFFINE>), grid, block, 0, s, ctx->g, p, cc, partials);
         break;
     case 2 * 16 + GALS_VEL_STREAM_SIN:
-        hipLaunchKernelGGL((k_max_speed<T, 2, GALS_VEL_STREAM_SIN>), grid, block, 0, s, ctx->g, p, cc, partials);
+        hipLaunchKernelGGL((k_max_speed_stream<T>), grid, block, 0, s, ctx->g, p, cc, partials);
         break;
     case 2 * 16 + GALS_VEL_VORTEX:
         hipLaunchKernelGGL((k_max_speed<T, 2, GALS_VEL_VORTEX>), grid, block, 0, s, ctx->g, p, cc, partials);
