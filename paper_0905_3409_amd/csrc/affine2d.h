@@ -165,8 +165,9 @@ __device__ __forceinline__ void split_disp(const Geom &g, const int *idx, const 
 }
 
 // Cell data from staged nodes (node-interleaved: a node's phi, psi_x, psi_y
-// side by side) with t0 and t1 at the cell's lower-left and upper-left node:
-// every neighbour sits at a fixed offset from one of the two. The central
+// side by side) with t0 and t1 at the node before the cell's lower-left and
+// upper-left one (LDS offsets are not negative): every neighbour sits at a fixed
+// offset from one of the two. The central
 // cross derivative reads one column beyond each side of the cell; at the
 // first and last cell of a row that column lies outside the grid, and the
 // one-sided differences used there do not read it (same values as gather2d).
@@ -174,8 +175,8 @@ template <typename T, int MIX>
 __device__ __forceinline__ void gather2d_lds(const Geom &g, const T *t0, const T *t1, int cx,
                                              T d[4][4])
 {
-    auto lo_ = [&](int k, int f) { return t0[3 * k + f]; };
-    auto up_ = [&](int k, int f) { return t1[3 * k + f]; };
+    auto lo_ = [&](int k, int f) { return t0[3 * (k + 1) + f]; };
+    auto up_ = [&](int k, int f) { return t1[3 * (k + 1) + f]; };
     d[0][0] = lo_(0, 0); d[1][0] = lo_(1, 0); d[2][0] = up_(0, 0); d[3][0] = up_(1, 0);
     d[0][1] = lo_(0, 1); d[1][1] = lo_(1, 1); d[2][1] = up_(0, 1); d[3][1] = up_(1, 1);
     if constexpr (MIX == GALS_MIXED_CENTRAL) {
@@ -202,6 +203,39 @@ __device__ __forceinline__ void gather2d_lds(const Geom &g, const T *t0, const T
         } else {
             d[0][3] = d[1][3] = d[2][3] = d[3][3] = T(0);
         }
+    }
+}
+
+// Value and gradient of the bicubic of cell c from staged nodes (FOLD as in
+// bicubic).
+template <typename T, int MIX, bool FOLD>
+__device__ __forceinline__ void bicubic_lds(const Geom &g, const T *t0, const T *t1, const int *c,
+                                            const T *xi, T &H, T &Hx, T &Hy)
+{
+    if constexpr (FOLD) {
+        const int xm = c[0] == 0 ? 3 : 0;  // the window starts at node 0 at the first cell
+        bicubic_central<T>(
+            g, c[0], xi,
+            [&](int r) {
+                const T *t = r ? t1 : t0;
+                Row2d<T> q;
+#pragma unroll
+                for (int k = 0; k < 4; k++) q.gy[k] = t[3 * k + 2 + xm];
+#pragma unroll
+                for (int k = 0; k < 2; k++) {
+                    q.phi[k] = t[3 * (k + 1)];
+                    q.gx[k] = t[3 * (k + 1) + 1];
+                }
+                return q;
+            },
+            [&](int vx, int vy) { return (vy ? t1 : t0)[3 * (vx + 1)]; }, H, Hx, Hy);
+    } else {
+        T d[4][4];
+        gather2d_lds<T, MIX>(g, t0, t1, c[0], d);
+        Basis<T> bx, by;
+        basis<T, false>(xi[0], geo_h<T>(g, 0), geo_ih<T>(g, 0), bx);
+        basis<T, false>(xi[1], geo_h<T>(g, 1), geo_ih<T>(g, 1), by);
+        hermite2d(d, bx, by, H, Hx, Hy);
     }
 }
 
@@ -251,18 +285,12 @@ __device__ __forceinline__ void affine_foot(const Geom &g, const AffineMap2<T> &
     }
 }
 
-// The bicubic of the gathered cell data and the gradient update: phi, psi_x,
-// psi_y.
+// The boundary treatment of the bicubic's gradient and the gradient update: phi,
+// psi_x, psi_y.
 template <typename T, int PSI>
-__device__ __forceinline__ void affine_values(const Geom &g, const AffineMap2<T> &am, double dt,
-                                              const T *xi, const bool *outb, const T (&d)[4][4],
-                                              T *out)
+__device__ __forceinline__ void affine_values(const AffineMap2<T> &am, double dt, const bool *outb,
+                                              T H, T Hx, T Hy, T *out)
 {
-    Basis<T> bx, by;
-    basis<T, false>(xi[0], geo_h<T>(g, 0), geo_ih<T>(g, 0), bx);
-    basis<T, false>(xi[1], geo_h<T>(g, 1), geo_ih<T>(g, 1), by);
-    T H, Hx, Hy;
-    hermite2d(d, bx, by, H, Hx, Hy);
     if (outb[0]) Hx = T(0);
     if (outb[1]) Hy = T(0);
     out[0] = H;

@@ -186,6 +186,15 @@ __device__ __forceinline__ void heun_gradient(const T *Af, const T *An, T dtT, c
     }
 }
 
+// Keep values computed here: the compiler would sink the Jacobian chain past the
+// interpolation's branches to its use after them, and hold the stage Jacobians
+// across the gather instead of their product.
+template <typename T>
+__device__ __forceinline__ void pin4(T *v)
+{
+    asm volatile("" : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]));
+}
+
 // ---------------------------------------------------------------------------
 // Homogeneous Neumann treatment of a foot outside the domain: project it onto
 // the domain and remember the axes whose normal derivative must vanish. A
@@ -753,6 +762,13 @@ __device__ __forceinline__ void tricubic_central(const Geom &g, Rsrc rphi, Rsrc 
     };
     Acc A[2] = {};
     T ref = T(0), p0 = T(0), p1 = T(0), p2 = T(0);  // phi and its gradient at the first vertex
+    // a foot on the far vertex along an axis (a node of the grid's last row or
+    // plane) takes that vertex's phi as the reference: an exact shift stays exact
+    T far_phi = T(0);
+    const bool far_side = !SECOND && (xi[0] == T(1) || xi[1] == T(1) || xi[2] == T(1));
+    if (__builtin_expect(far_side, 0))
+        far_phi = bload(rphi, o0 + (xi[0] == T(1) ? 1u : 0u) + (xi[1] == T(1) ? P : 0u) +
+                                  (xi[2] == T(1) ? S : 0u), T());
     const T gh[3] = {geo_h<T>(g, 0), geo_h<T>(g, 1), geo_h<T>(g, 2)};
     auto dot = [](const T *u, const T *w) { return u[0] * w[0] + u[1] * w[1] + u[2] * w[2] + u[3] * w[3]; };
     auto sums = [&](Acc &a, bool first, T x0, T x1, T x2, T wy, T dwy, T ddwy) {
@@ -781,7 +797,7 @@ __device__ __forceinline__ void tricubic_central(const Geom &g, Rsrc rphi, Rsrc 
         } else {
             const int vy = part - 2;
             if (q == 2) {
-                ref = u[4];
+                ref = far_side ? far_phi : u[4];
                 if constexpr (SECOND) {
                     p0 = u[6];
                     p1 = xlo ? u[0] : u[1];
@@ -851,6 +867,107 @@ __device__ __forceinline__ void tricubic_central(const Geom &g, Rsrc rphi, Rsrc 
     }
     H = ref + h;
     G[0] = hx; G[1] = hy; G[2] = hz;
+}
+
+// ---------------------------------------------------------------------------
+// The bicubic with central cross derivatives in the same form, for FP64 states:
+// psi_y a 4 x 2 stencil, phi as differences from one vertex, a row's samples by
+// wide loads. FP32 states keep gather2d and hermite2d (another rounding of phi
+// shows in psi as u |phi| / h), and so does the affine step, whose gather is in
+// LDS: 19 more registers cost its FP64 kernel two waves per SIMD (513^2 186 -> 190
+// us per 32 steps). 1729^2 FP64 stream function: 64 us per step with
+// gather2d and hermite2d, 60 with this (VALU instructions per wave 539 ->
+// 507, the address unit busy 73 % -> 64 % of the launch).
+// ---------------------------------------------------------------------------
+template <typename T, int MIX>
+constexpr bool kFold2d = sizeof(T) == 8 && MIX == GALS_MIXED_CENTRAL;
+
+// One row of the cell: phi and psi_x at c and c + 1, psi_y at the four nodes of the
+// window (c - 1 .. c + 2, or 0 .. 3 at the first cell).
+template <typename T>
+struct Row2d {
+    T phi[2], gx[2], gy[4];
+};
+
+// row(r) gives row r = 0, 1, phi(vx, vy) a vertex's phi.
+template <typename T, class Row, class Phi>
+__device__ __forceinline__ void bicubic_central(const Geom &g, int cx, const T *xi, Row row, Phi phi,
+                                                T &H, T &Hx, T &Hy)
+{
+    Basis<T> bx, by;
+    basis<T, false>(xi[0], geo_h<T>(g, 0), geo_ih<T>(g, 0), bx);
+    basis<T, false>(xi[1], geo_h<T>(g, 1), geo_ih<T>(g, 1), by);
+    const bool lo = cx == 0, hi = cx + 1 == g.nc[0], edge = lo || hi;
+    const T i2h = geo_i2h<T>(g, 0);
+    T w[4], dw[4];
+    stencil_weights(bx.w, i2h, lo, hi, w);
+    stencil_weights(bx.dw, i2h, lo, hi, dw);
+    if (__builtin_expect(lo, 0)) {
+#pragma unroll
+        for (int k = 0; k < 3; k++) {
+            w[k] = w[k + 1];
+            dw[k] = dw[k + 1];
+        }
+    }
+    // the vertex the foot is on, if it is on a far one (see tricubic_central)
+    T ref = phi(0, 0);
+    if (__builtin_expect(xi[0] == T(1) || xi[1] == T(1), 0))
+        ref = phi(xi[0] == T(1) ? 1 : 0, xi[1] == T(1) ? 1 : 0);
+    T h = 0, hx = 0, hy = 0;
+#pragma unroll
+    for (int r = 0; r < 2; r++) {
+        const Row2d<T> q = row(r);
+        const T u[4] = {q.gy[0], q.gy[1], q.gy[2], edge ? T(0) : q.gy[3]};
+        const T y0 = u[0] * w[0] + u[1] * w[1] + u[2] * w[2] + u[3] * w[3];
+        const T y1 = u[0] * dw[0] + u[1] * dw[1] + u[2] * dw[2] + u[3] * dw[3];
+        const T du = q.phi[1] - q.phi[0], p = q.phi[0] - ref;
+        const T x0 = p + du * bx.w[1] + q.gx[0] * bx.w[2] + q.gx[1] * bx.w[3];
+        const T x1 = du * bx.dw[1] + q.gx[0] * bx.dw[2] + q.gx[1] * bx.dw[3];
+        h += x0 * by.w[r];
+        h += y0 * by.w[2 + r];
+        hx += x1 * by.w[r];
+        hx += y1 * by.w[2 + r];
+        hy += x0 * by.dw[r];
+        hy += y0 * by.dw[2 + r];
+    }
+    H = ref + h;
+    Hx = hx;
+    Hy = hy;
+}
+
+// Value and gradient of the bicubic of cell c at local coordinates xi, for any
+// precision and cross-derivative rule, from the planes. FOLD as kFold2d, or false
+// for the form with explicit cross derivatives.
+template <typename T, int MIX, bool FOLD = kFold2d<T, MIX>>
+__device__ __forceinline__ void bicubic(const Geom &g, Rsrc rphi, Rsrc rgx, Rsrc rgy, const int *c,
+                                        const T *xi, T &H, T &Hx, T &Hy)
+{
+    if constexpr (FOLD) {
+        const unsigned o = unsigned(c[1]) * unsigned(g.pitch) + unsigned(c[0]);
+        const unsigned xm = c[0] == 0 ? 0u : 1u;
+        Row2d<T> q[2];
+#pragma unroll
+        for (int r = 0; r < 2; r++) {
+            const unsigned ro = o + (r ? unsigned(g.pitch) : 0u);
+            bload4(rgy, ro - xm, q[r].gy);
+            bload2(rphi, ro, q[r].phi);
+            bload2(rgx, ro, q[r].gx);
+        }
+        bicubic_central<T>(
+            g, c[0], xi, [&](int r) { return q[r]; },
+            [&](int vx, int vy) {
+                const T a = vx ? q[0].phi[1] : q[0].phi[0], b = vx ? q[1].phi[1] : q[1].phi[0];
+                return vy ? b : a;
+            },
+            H, Hx, Hy);
+    } else {
+        T d[4][4];
+        gather2d<T, MIX>(g, rphi, rgx, rgy, c[0], c[1], d);
+        Basis<T> bx, by;
+        basis<T, false>(xi[0], geo_h<T>(g, 0), geo_ih<T>(g, 0), bx);
+        basis<T, false>(xi[1], geo_h<T>(g, 1), geo_ih<T>(g, 1), by);
+        hermite2d(d, bx, by, H, Hx, Hy);
+    }
 }
 
 // Value and gradient of the tricubic of cell c at local coordinates xi, for

@@ -43,17 +43,13 @@ __global__ __launch_bounds__(kBlock) void k_step2d(Geom g, Vel<T> p, Stage<T> st
     const unsigned out = project_foot<2>(g, X);
 
     int cell[2];
-    double xi[2];
-    split<2>(g, X, cell, xi);
-
-    T d[4][4];
-    gather2d<T, MIX>(g, plane_rsrc(phi, g.plane), plane_rsrc(gx, g.plane), plane_rsrc(gy, g.plane),
-                     cell[0], cell[1], d);
-    Basis<T> bx, by;
-    basis<T, false>(T(xi[0]), geo_h<T>(g, 0), geo_ih<T>(g, 0), bx);
-    basis<T, false>(T(xi[1]), geo_h<T>(g, 1), geo_ih<T>(g, 1), by);
+    double xid[2];
+    split<2>(g, X, cell, xid);
+    const T xi[2] = {T(xid[0]), T(xid[1])};
+    if constexpr (kFold2d<T, MIX>) pin4(J);
     T H, Hx, Hy;
-    hermite2d(d, bx, by, H, Hx, Hy);
+    bicubic<T, MIX>(g, plane_rsrc(phi, g.plane), plane_rsrc(gx, g.plane), plane_rsrc(gy, g.plane),
+                    cell, xi, H, Hx, Hy);
     if (out & 1u) Hx = T(0);
     if (out & 2u) Hy = T(0);
 
@@ -222,9 +218,9 @@ __global__ __launch_bounds__(kBlock) void k_step2d_affine(Geom g, TileGrid tg, A
         // the Hermite evaluation and the update from the cell data of either
         // source; each source finishes on its own (merging the two sources'
         // cell data before one evaluation cost register moves on every lane)
-        auto finish = [&](const T (&d)[4][4]) {
+        auto finish = [&](T H, T Hx, T Hy) {
             T v[3];
-            affine_values<T, PSI>(g, am, dt, xi[r], outb[r], d, v);
+            affine_values<T, PSI>(am, dt, outb[r], H, Hx, Hy, v);
             if (!store) return;
             const unsigned o = unsigned(j) * unsigned(g.pitch) + unsigned(i);
             pstore_nt(phi_o, o, v[0]);
@@ -232,15 +228,15 @@ __global__ __launch_bounds__(kBlock) void k_step2d_affine(Geom g, TileGrid tg, A
             pstore_nt(grad_o + g.plane, o, v[2]);
         };
         if (__builtin_expect(on, 1)) {
-            T d[4][4];
-            const T *t = tile + 3 * ((cy - ry0) * S::W + (cx - cx0));
-            gather2d_lds<T, MIX>(g, t, t + 3 * S::W, cx, d);
-            finish(d);
+            T H, Hx, Hy;
+            const T *t = tile + 3 * ((cy - ry0) * S::W + (cx - 1 - cx0));
+            bicubic_lds<T, MIX, false>(g, t, t + 3 * S::W, cell[r], xi[r], H, Hx, Hy);
+            finish(H, Hx, Hy);
         } else {
-            T d[4][4];
-            gather2d<T, MIX>(g, plane_rsrc(phi, g.plane), plane_rsrc(gx, g.plane),
-                             plane_rsrc(gy, g.plane), cx, cy, d);
-            finish(d);
+            T H, Hx, Hy;
+            bicubic<T, MIX, false>(g, plane_rsrc(phi, g.plane), plane_rsrc(gx, g.plane),
+                                   plane_rsrc(gy, g.plane), cell[r], xi[r], H, Hx, Hy);
+            finish(H, Hx, Hy);
         }
     }
 }

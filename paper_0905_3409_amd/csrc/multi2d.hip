@@ -128,10 +128,10 @@ __device__ __forceinline__ void multi_node(const Geom &g, const AffineSteps<T> &
     T xi[2];
     bool outb[2];
     affine_foot(g, am, i, j, cell, xi, outb);
-    T d[4][4];
-    const T *t = buf + 3 * ((cell[1] - R.y0) * w + (cell[0] - R.x0));
-    gather2d_lds<T, MIX>(g, t, t + 3 * w, cell[0], d);
-    affine_values<T, PSI>(g, am, dt, xi, outb, d, out);
+    T H, Hx, Hy;
+    const T *t = buf + 3 * ((cell[1] - R.y0) * w + (cell[0] - 1 - R.x0));
+    bicubic_lds<T, MIX, false>(g, t, t + 3 * w, cell, xi, H, Hx, Hy);
+    affine_values<T, PSI>(am, dt, outb, H, Hx, Hy, out);
 }
 
 template <typename T, int MIX, int PSI>
@@ -143,10 +143,11 @@ __device__ __forceinline__ void multi_node(const Geom &g, const StreamSteps<T> &
     const T *U = f.coltab + i * kJet, *Y = f.rowtab + j * kJet;
     StreamFoot<T> ft;
     stream_trace<T, sizeof(T) == 4, PSI == GALS_PSI_SUPERCONSISTENT>(g, f, st, dt, U, Y, i, j, ft);
-    T d[4][4];
-    const T *t = buf + 3 * ((ft.cell[1] - R.y0) * w + (ft.cell[0] - R.x0));
-    gather2d_lds<T, MIX>(g, t, t + 3 * w, ft.cell[0], d);
-    stream_values<T, sizeof(T) == 4, PSI>(g, f, st, dt, U, Y, ft, d, i, j,
+    if constexpr (kFold2d<T, MIX> && PSI == GALS_PSI_SUPERCONSISTENT) pin4(ft.J);
+    T H, Hx, Hy;
+    const T *t = buf + 3 * ((ft.cell[1] - R.y0) * w + (ft.cell[0] - 1 - R.x0));
+    bicubic_lds<T, MIX, kFold2d<T, MIX>>(g, t, t + 3 * w, ft.cell, ft.xi, H, Hx, Hy);
+    stream_values<T, sizeof(T) == 4, PSI>(g, f, st, dt, U, Y, ft, H, Hx, Hy, i, j,
                                           [&](int q, T v) { out[q] = v; });
 }
 

@@ -305,8 +305,8 @@ __device__ __forceinline__ void stream_trace(const Geom &g, const P &p, const St
     }
 }
 
-// The part of a stream-function step after the trace and the gather: the
-// bicubic, the boundary treatment of its gradient, and the update
+// The part of a stream-function step after the trace and the bicubic: the
+// boundary treatment of its gradient, and the update
 // (superconsistent, or Heun's method with grad v at the foot from the node's
 // jet). put(f, value) takes phi, psi_x, psi_y (f = 0, 1, 2), each as soon as it
 // is known.
@@ -314,13 +314,8 @@ template <typename T, bool TAYLOR, int PSI, class P, class Put>
 __device__ __forceinline__ void stream_values(const Geom &g, const P &p, const Stage<T> &st,
                                               double dt, const T *__restrict__ U,
                                               const T *__restrict__ Y, const StreamFoot<T> &f,
-                                              const T (&d)[4][4], int i, int j, Put put)
+                                              T H, T Hx, T Hy, int i, int j, Put put)
 {
-    Basis<T> bx, by;
-    basis<T, false>(T(f.xi[0]), geo_h<T>(g, 0), geo_ih<T>(g, 0), bx);
-    basis<T, false>(T(f.xi[1]), geo_h<T>(g, 1), geo_ih<T>(g, 1), by);
-    T H, Hx, Hy;
-    hermite2d(d, bx, by, H, Hx, Hy);
     if (f.outb[0]) Hx = T(0);
     if (f.outb[1]) Hy = T(0);
     put(0, H);
@@ -346,12 +341,12 @@ template <typename T, bool TAYLOR, int PSI, class P>
 __device__ __forceinline__ void stream_store(const Geom &g, const P &p, const Stage<T> &st,
                                              double dt, const T *__restrict__ U,
                                              const T *__restrict__ Y, const StreamFoot<T> &f,
-                                             const T (&d)[4][4], T *__restrict__ phi_o,
+                                             T H, T Hx, T Hy, T *__restrict__ phi_o,
                                              T *__restrict__ gx_o, T *__restrict__ gy_o, int i,
                                              int j)
 {
     const unsigned o = unsigned(j) * unsigned(g.pitch) + unsigned(i);
-    stream_values<T, TAYLOR, PSI>(g, p, st, dt, U, Y, f, d, i, j, [&](int q, T v) {
+    stream_values<T, TAYLOR, PSI>(g, p, st, dt, U, Y, f, H, Hx, Hy, i, j, [&](int q, T v) {
         pstore(q == 0 ? phi_o : q == 1 ? gx_o : gy_o, o, v);
     });
 }
@@ -369,12 +364,13 @@ __device__ __forceinline__ void stream_node(const Geom &g, const P &p, const Sta
 {
     StreamFoot<T> f;
     stream_trace<T, TAYLOR, PSI == GALS_PSI_SUPERCONSISTENT>(g, p, st, dt, U, Y, i, j, f);
-    T d[4][4];
+    if constexpr (kFold2d<T, MIX> && PSI == GALS_PSI_SUPERCONSISTENT) pin4(f.J);
+    T H, Hx, Hy;
     // buffer resources made here, not before the trace, so that they are not
     // held in scalar registers across it
-    gather2d<T, MIX>(g, plane_rsrc(phi, g.plane), plane_rsrc(gx, g.plane),
-                     plane_rsrc(gy, g.plane), f.cell[0], f.cell[1], d);
-    stream_store<T, TAYLOR, PSI>(g, p, st, dt, U, Y, f, d, phi_o, gx_o, gy_o, i, j);
+    bicubic<T, MIX>(g, plane_rsrc(phi, g.plane), plane_rsrc(gx, g.plane), plane_rsrc(gy, g.plane),
+                    f.cell, f.xi, H, Hx, Hy);
+    stream_store<T, TAYLOR, PSI>(g, p, st, dt, U, Y, f, H, Hx, Hy, phi_o, gx_o, gy_o, i, j);
 }
 
 // Workgroups are dealt to the 8 XCDs round-robin by id, and each XCD has its
