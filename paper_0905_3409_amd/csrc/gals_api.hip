@@ -161,9 +161,6 @@ hipError_t advance_core(const gals_ctx *ctx, void *phi, void *grad, double t0, d
             took = 1;
             e = launch_step(ctx, src[0], src[1], dst[0], dst[1], dt, c[0][0], c[0][1], c[0][2],
                             coltab, rowtab, s);
-            if (e == hipSuccess && ctx->inflow) e = launch_inflow(ctx, dst[0], dst[1], c[0][0], dt, s);
-            if (e == hipSuccess && ctx->face)
-                e = launch_face(ctx, src[0], src[1], dst[0], dst[1], dt, c[0][0], c[0][1], c[0][2], s);
         }
         if (e != hipSuccess) return e;
         n += took;

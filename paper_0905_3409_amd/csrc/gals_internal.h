@@ -220,7 +220,8 @@ namespace gals {
 // Thread-local error text returned by gals_last_error() (gals_api.hip).
 void set_error_v(const char *fmt, va_list ap);
 
-// Launchers (kernels_*.hip). Each returns a hipError_t of the launch.
+// Launchers (kernels_*.hip). Each returns a hipError_t of the launch. launch_step
+// applies the context's inflow conditions as well.
 hipError_t launch_step(const gals_ctx *ctx, const void *phi, const void *grad, void *phi_o,
                        void *grad_o, double dt, double c1, double c2, double c3,
                        const void *coltab, const void *rowtab, hipStream_t s);

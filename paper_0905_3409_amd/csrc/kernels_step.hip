@@ -9,15 +9,25 @@
 // number of cells away are gathered from global memory, so every CFL number
 // is handled.
 #include "affine2d.h"
+#include "boundary.h"
 #include "stream2d.h"
 
 namespace gals {
 
+// Inflow conditions that a step kernel applies itself, to its boundary nodes
+// after their step: the dependent launch for a few hundred nodes took 3.5 us
+// beside 4 to 5 for the step of a small grid (258 x 182 FP64 1D-like field,
+// Dirichlet, 5 steps: 44 us with k_inflow, 29.5 with this; 806 x 1006 FP32
+// vortex, Neumann, 3 steps: 62 and 53). The general 2D kernel only: the other
+// fields' step kernels are at their register limits, and the conditions are
+// theirs through boundary.hip.
+enum { kBcNone = 0, kBcInflow = 1, kBcFace = 2 };
+
 // Node index -> (i, j[, k]) with 32-bit arithmetic (the host caps the node
 // count below 2^31).
-template <typename T, int KIND, int MIX, int PSI>
+template <typename T, int KIND, int MIX, int PSI, int BC>
 __global__ __launch_bounds__(kBlock) void k_step2d(Geom g, Vel<T> p, Stage<T> st, double dt,
-                                                   const T *__restrict__ tab,
+                                                   InflowData<T> b, const T *__restrict__ tab,
                                                    const T *__restrict__ phi,
                                                    const T *__restrict__ grad,
                                                    T *__restrict__ phi_o, T *__restrict__ grad_o)
@@ -65,6 +75,14 @@ __global__ __launch_bounds__(kBlock) void k_step2d(Geom g, Vel<T> p, Stage<T> st
     } else {
         pstore(grad_o, o, J[0] * Hx + J[2] * Hy);
         pstore(grad_o + g.plane, o, J[1] * Hx + J[3] * Hy);
+    }
+    if constexpr (BC != kBcNone) {
+        if (i != 0 && i != g.nc[0] && j != 0 && j != g.nc[1]) return;
+        const int ij[2] = {i, j};
+        if constexpr (BC == kBcInflow)
+            inflow_node<T, 2, KIND>(g, p, st.c1, dt, ij, b, phi_o, grad_o);
+        else
+            face_node<T, 2, KIND, MIX>(g, p, st, dt, ij, phi, grad, phi_o, grad_o);
     }
 }
 
@@ -683,9 +701,12 @@ static hipError_t launch_typed(const gals_ctx *ctx, const Vel<T> &p, const void 
     }
     if (ctx->dim == 2) {
         if constexpr (KIND == GALS_VEL_VORTEX || KIND == GALS_VEL_PSEUDO1D) {
-            hipLaunchKernelGGL((k_step2d<T, KIND, MIX, PSI>), dim3(blocks), dim3(kBlock), 0, s,
-                               ctx->g, p, st, dt, (const T *)tab, (const T *)phi, (const T *)grad, (T *)phi_o,
-                               (T *)grad_o);
+            auto kern = ctx->inflow ? k_step2d<T, KIND, MIX, PSI, kBcInflow>
+                        : ctx->face ? k_step2d<T, KIND, MIX, PSI, kBcFace>
+                                    : k_step2d<T, KIND, MIX, PSI, kBcNone>;
+            hipLaunchKernelGGL(kern, dim3(blocks), dim3(kBlock), 0, s, ctx->g, p, st, dt,
+                               inflow_data<T>(ctx), (const T *)tab, (const T *)phi,
+                               (const T *)grad, (T *)phi_o, (T *)grad_o);
             return hipGetLastError();
         }
     } else {
@@ -726,7 +747,7 @@ hipError_t launch_step(const gals_ctx *ctx, const void *phi, const void *grad, v
 {
     const bool stream = ctx->vel_kind == GALS_VEL_STREAM_SIN && coltab && rowtab;
     const bool vecpot = ctx->dim == 3 && ctx->vel_kind == GALS_VEL_VECPOT_SIN && coltab;
-    return with_modes(ctx->mixed, ctx->psi, [&](auto mix, auto psi) -> hipError_t {
+    hipError_t e = with_modes(ctx->mixed, ctx->psi, [&](auto mix, auto psi) -> hipError_t {
         constexpr int MIX = decltype(mix)::value, PSI = decltype(psi)::value;
         if (vecpot)
             return ctx->prec == GALS_F32
@@ -746,6 +767,12 @@ hipError_t launch_step(const gals_ctx *ctx, const void *phi, const void *grad, v
                    : launch_kind<double, MIX, PSI>(ctx, ctx->vd, phi, grad, phi_o, grad_o, dt, c1,
                                                    c2, c3, coltab, s);
     });
+    // k_step2d has treated its boundary nodes
+    if (ctx->vel_kind == GALS_VEL_VORTEX || ctx->vel_kind == GALS_VEL_PSEUDO1D) return e;
+    if (e == hipSuccess && ctx->inflow) e = launch_inflow(ctx, phi_o, grad_o, c1, dt, s);
+    if (e == hipSuccess && ctx->face)
+        e = launch_face(ctx, phi, grad, phi_o, grad_o, dt, c1, c2, c3, s);
+    return e;
 }
 
 }  // namespace gals
