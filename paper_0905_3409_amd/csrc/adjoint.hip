@@ -202,6 +202,35 @@ __device__ __forceinline__ void emit_scatter(const double (&dbar)[4][4], int c0,
     }
 }
 
+// Tile of a block: runs of kChunk tiles (walked row group by row group) dealt
+// to the XCDs in turn, the last incomplete round of runs in plain order. A
+// band of tiles per XCD (xcd_tile) would share halo rows in fewer L2s, but the
+// live tiles (see the kernel) lie along curves and fill the bands unevenly:
+// gradient of a shape loss at 1025^2 FP32 1370 us with bands, 1183, 1169 and
+// 1167 with runs of 64, 16 and 1; a dense lambda is served alike by all three.
+constexpr unsigned kChunk = 16;
+__device__ __forceinline__ bool chunk_tile(const Geom &g, unsigned &tx, unsigned &ty)
+{
+    const unsigned b = blockIdx.x, first = b / (8u * kChunk) * (8u * kChunk);
+    unsigned t = b;
+    if (first + 8u * kChunk <= gridDim.x)
+        t = first + b % 8u * kChunk + (b - first) / 8u;
+    ty = __umulhi(t, g.tiles_x_magic);
+    tx = t - ty * g.tiles_x;
+    if (tx >= g.tiles_x) {
+        ty += 1u;
+        tx -= g.tiles_x;
+    }
+    return t < g.tiles;
+}
+
+// Bound by vector instruction issue (about 1690 VALU instructions per wave of
+// 64 nodes, FP32). The lambda of a shape loss is zero outside the band of the
+// interface, which a backward step widens by a cell or two, so a wave looks at
+// its lambda first: a step at 1025^2 FP32 takes 48 us when every wave has work
+// and 17 with 15 % of them live (a band of 6 cells to each side, 20 steps). The
+// look costs a lambda without zeros 1 % (10 steps and the recomputed states
+// 620 -> 627 us).
 // Four waves per SIMD in FP32 (at most 128 VGPRs): an earlier form took 134
 // and three waves by default, 80 us per step on the 1024^2 gradient workload
 // against 68 at four. The FP64 kernel would spill heavily and keeps the
@@ -214,22 +243,38 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
     double *__restrict__ lam_in, double *__restrict__ lam_out, double *__restrict__ partials)
 {
     unsigned tx, ty;
-    const bool in_grid = xcd_tile(g, tx, ty);
+    const bool in_grid = chunk_tile(g, tx, ty);
     const int i = int(tx) * 64 + int(threadIdx.x & 63u);
     const int j = __builtin_amdgcn_readfirstlane(int(ty) * 4 + int(threadIdx.x >> 6));
     double gacc[16];
-#pragma unroll
-    for (int q = 0; q < 16; q++) gacc[q] = 0.0;
     double dbar[4][4];
     int cell0 = 0, cell1 = 0;
-    const bool valid = in_grid && i < g.n[0] && j < g.n[1];
+    const bool in_row = in_grid && i < g.n[0] && j < g.n[1];
+    const int64_t o = int64_t(j) * g.pitch + i;
+    double lf = 0.0, lx = 0.0, ly = 0.0;
+    if (in_row) {
+        lf = lam_in[o];
+        lx = lam_in[o + g.plane];
+        ly = lam_in[o + 2 * g.plane];
+    }
+    // A wave whose lambda is all +0 has nothing to add: its shares and its
+    // parameter derivative are products with lambda. It skips the trace, and
+    // a block of such waves the rest; data that are not finite still reach the
+    // derivative as 0 times them.
+    const uint64_t bits = __builtin_bit_cast(uint64_t, lf) | __builtin_bit_cast(uint64_t, lx) |
+                          __builtin_bit_cast(uint64_t, ly);
+    const bool live = __builtin_amdgcn_ballot_w64(bits != 0) != 0;
+    double poison = 0.0;
+    if (!live && in_row)
+        poison = double(T(0) * phi[o] + T(0) * grad[o] + T(0) * (grad + g.plane)[o]);
+#pragma unroll
+    for (int q = 0; q < 16; q++) gacc[q] = poison;
+    const bool valid = in_row && live;
 
     if (valid) {
         StreamFoot<T> f;
         stream_trace<T, TAYLOR>(g, p, st, dt, coltab + int64_t(i) * kJet,
                                 rowtab + int64_t(j) * kJet, i, j, f);
-        const int64_t o = int64_t(j) * g.pitch + i;
-        const double lf = lam_in[o], lx = lam_in[o + g.plane], ly = lam_in[o + 2 * g.plane];
         if constexpr (CLEAR) {
             lam_in[o] = 0.0;
             lam_in[o + g.plane] = 0.0;
@@ -253,14 +298,18 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
         // lambda_phi W + mu . grad W (scattered below)
         cell0 = f.cell[0];
         cell1 = f.cell[1];
+        double wl[4], wm[4];
+#pragma unroll
+        for (int k = 0; k < 4; k++) {
+            wl[k] = lf * double(bx.w[k]) + mu0 * double(bx.dw[k]);
+            wm[k] = mu1 * double(bx.w[k]);
+        }
 #pragma unroll
         for (int v = 0; v < 4; v++)
 #pragma unroll
             for (int a = 0; a < 4; a++) {
                 const int kx = (v & 1) + 2 * (a & 1), ky = (v >> 1) + 2 * (a >> 1);
-                dbar[v][a] = lf * double(bx.w[kx]) * double(by.w[ky]) +
-                             mu0 * double(bx.dw[kx]) * double(by.w[ky]) +
-                             mu1 * double(bx.w[kx]) * double(by.dw[ky]);
+                dbar[v][a] = wl[kx] * double(by.w[ky]) + wm[kx] * double(by.dw[ky]);
             }
         if constexpr (MIX == GALS_MIXED_CELL) {
             // transpose of approach (B): phi_xy[v] = 3/4 (ea[vx] + eb[vy])
@@ -379,29 +428,35 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
     // with one global atomic per node and field: about 4x fewer global
     // atomics. Boxes larger than the tile fall back to direct atomics.
     __shared__ double s_tile[3 * kTileH * kTileW];
-    __shared__ int s_box[4];
+    __shared__ int s_box[4], s_poison;
     if (threadIdx.x == 0) {
+        s_poison = 0;
         s_box[0] = s_box[2] = 0x7fffffff;
         s_box[1] = s_box[3] = -0x7fffffff;
     }
     __syncthreads();
     {
         // min of cell0, -cell0, cell1, -cell1 over the block's nodes (the
-        // neutral element of min for lanes without a node)
+        // neutral element of min for lanes without a node; a wave that is not
+        // live leaves the box as it is)
         int b[4] = {valid ? cell0 : 0x7fffffff, valid ? -cell0 : 0x7fffffff,
                     valid ? cell1 : 0x7fffffff, valid ? -cell1 : 0x7fffffff};
+        if (live) {
 #pragma unroll
-        for (int k = 0; k < 4; k++) b[k] = wave_min(b[k]);
-        if ((threadIdx.x & 63u) == 0) {
+            for (int k = 0; k < 4; k++) b[k] = wave_min(b[k]);
+        }
+        if (live && (threadIdx.x & 63u) == 0) {
             atomicMin(&s_box[0], b[0]);
             atomicMax(&s_box[1], -b[1]);
             atomicMin(&s_box[2], b[2]);
             atomicMax(&s_box[3], -b[3]);
         }
+        if (poison != 0.0) s_poison = 1;
     }
     __syncthreads();
     // the block has nodes: then all four are cell indices in [0, nc - 1]
     const bool any = s_box[0] <= s_box[1] && s_box[2] <= s_box[3];
+    if (!any && !s_poison) return;
     const int bx0 = s_box[0] - 1, by0 = s_box[2];
     const int bw = any ? s_box[1] - s_box[0] + 4 : 0, bh = any ? s_box[3] - s_box[2] + 2 : 0;
     const double inv2h = double(geo_i2h<T>(g, 0));
