@@ -484,26 +484,28 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
     block_sum16<true>(gacc, partials + int64_t(blockIdx.x) * 16);
 }
 
-// Parameter-derivative partials: sum over blocks in a fixed order. Thread t
-// takes slot t % 16 of the partials t / 16, t / 16 + 64, ..., so a pass reads 8 KB
-// in a row, then 64 sums per slot are folded in order. 4352 partials (a 1025^2
-// grid): 20 us with one partial a thread and pass, 12 with this.
+// Parameter-derivative partials: sum over blocks in a fixed order. Block `slot`
+// sums its slot of every partial, thread t of the partials t, t + 1024, ...,
+// then over the lanes of each wave and the waves. 4352 partials (a 1025^2 grid)
+// are 557 KB: 12 to 16 us by one block for all slots, 7.6 by 16.
 constexpr int kFoldThreads = 1024;
 __global__ __launch_bounds__(kFoldThreads) void k_fold_grad(const double *__restrict__ partials,
                                                             int nparts, double *__restrict__ out)
 {
-    __shared__ double sm[kFoldThreads / 16][16];
-    const int slot = int(threadIdx.x) & 15, b0 = int(threadIdx.x) >> 4;
+    __shared__ double sm[kFoldThreads / 64];
+    const int slot = int(blockIdx.x), t = int(threadIdx.x);
     double acc = 0.0;
-#pragma unroll 8
-    for (int b = b0; b < nparts; b += kFoldThreads / 16) acc += partials[int64_t(b) * 16 + slot];
-    sm[b0][slot] = acc;
+#pragma unroll 4
+    for (int b = t; b < nparts; b += kFoldThreads) acc += partials[int64_t(b) * 16 + slot];
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
+    if ((t & 63) == 0) sm[t >> 6] = acc;
     __syncthreads();
-    if (threadIdx.x < 16) {
+    if (t == 0) {
         double v = 0.0;
-#pragma unroll 8
-        for (int k = 0; k < kFoldThreads / 16; k++) v += sm[k][threadIdx.x];
-        out[threadIdx.x] += v;
+#pragma unroll
+        for (int k = 0; k < kFoldThreads / 64; k++) v += sm[k];
+        out[slot] += v;
     }
 }
 
@@ -597,7 +599,7 @@ hipError_t launch_adjoint_step(const gals_ctx *ctx, const void *phi, const void 
 
 hipError_t launch_fold_grad(const double *partials, int nparts, double *out, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_fold_grad, dim3(1), dim3(kFoldThreads), 0, s, partials, nparts, out);
+    hipLaunchKernelGGL(k_fold_grad, dim3(16), dim3(kFoldThreads), 0, s, partials, nparts, out);
     return hipGetLastError();
 }
 

@@ -120,32 +120,32 @@ void table_slots(const gals_ctx *ctx, int64_t steps, void *workspace, void *&col
     }
 }
 
+struct Planes {
+    void *phi, *grad;
+};
+
 // Steps n_begin .. n_end-1 of an advance of `steps` steps from time t0 (step n
-// starts at t0 + n dt), ping-ponging through the workspace's state copy; the
-// result ends in (phi, grad). Builds the field's tables first if `tables`, else
-// they must be in the workspace already.
-hipError_t advance_core(const gals_ctx *ctx, void *phi, void *grad, double t0, double dt,
-                        int64_t n_begin, int64_t n_end, int64_t steps, bool tables,
+// starts at t0 + n dt), from the state in `from` (which may be `state` or a
+// buffer of its own that is only read) into `to` (`state` or a buffer of its
+// own), ping-ponging between `state` and the workspace's state copy. The
+// field's tables must be in the workspace.
+hipError_t advance_core(const gals_ctx *ctx, Planes state, Planes from, Planes to, double t0,
+                        double dt, int64_t n_begin, int64_t n_end, int64_t steps, int64_t left,
                         void *workspace, hipStream_t s)
 {
     const size_t pb = size_t(ctx->g.plane) * elem_size(ctx);
     char *ws = (char *)workspace;
-    void *bufs[2][2] = {{phi, grad}, {ws, ws + pb}};
+    const Planes bufs[2] = {state, {ws, ws + pb}};
     void *coltab, *rowtab;
     table_slots(ctx, steps, workspace, coltab, rowtab);
     const int most = multi_steps(ctx, dt);  // steps a launch may take
-    // an even number of launches from the caller's buffers, or an odd one from
-    // the workspace's copy, ends in the caller's buffers
-    int64_t left = (n_end - n_begin + most - 1) / most;
-    if ((left & 1) && left < n_end - n_begin) left++;
-    int cur = int(left & 1);  // the buffers that hold the state
-    hipError_t e = launch_prepare(ctx, tables ? coltab : nullptr, rowtab, phi, grad,
-                                  cur ? ws : nullptr, s);
-    if (e != hipSuccess) return e;
+    hipError_t e = hipSuccess;
     for (int64_t n = n_begin; n < n_end;) {
         int64_t want = left > 1 ? (n_end - n + left - 1) / left : n_end - n;
         if (want > most) want = most;
-        void **src = bufs[cur], **dst = bufs[cur ^ 1];
+        // the last launch writes `to`, the one before it the workspace, and so on
+        Planes dst = n + want == n_end ? to : bufs[(left - 1) & 1];
+        if (dst.phi == from.phi) dst = bufs[from.phi == bufs[0].phi];
         double c[kMultiSteps][3];
         for (int q = 0; q < want; q++) {
             const double t = t0 + double(n + q) * dt;
@@ -155,30 +155,58 @@ hipError_t advance_core(const gals_ctx *ctx, void *phi, void *grad, double t0, d
         }
         int took = 0;
         if (want > 1)
-            e = launch_multi_step(ctx, int(want), c, src[0], src[1], dst[0], dst[1], dt, coltab, rowtab,
-                                  s, &took);
+            e = launch_multi_step(ctx, int(want), c, from.phi, from.grad, dst.phi, dst.grad, dt,
+                                  coltab, rowtab, s, &took);
         if (e == hipSuccess && took == 0) {
             took = 1;
-            e = launch_step(ctx, src[0], src[1], dst[0], dst[1], dt, c[0][0], c[0][1], c[0][2],
-                            coltab, rowtab, s);
+            e = launch_step(ctx, from.phi, from.grad, dst.phi, dst.grad, dt, c[0][0], c[0][1],
+                            c[0][2], coltab, rowtab, s);
         }
         if (e != hipSuccess) return e;
         n += took;
         left--;
-        cur ^= 1;
+        from = dst;
     }
-    if (cur) {
-        // a launch took fewer steps than planned and the result sits in the
-        // workspace: copy the valid part of each plane back
+    if (from.phi != to.phi) {
+        // a launch took fewer steps than planned and the result sits elsewhere:
+        // copy the valid part of each plane
         const size_t es = elem_size(ctx);
         const size_t w = size_t(ctx->g.n[0]) * es, p = size_t(ctx->g.pitch) * es;
         const size_t rows = size_t(ctx->g.n[1]) * size_t(ctx->g.n[2]);
         for (int a = 0; a <= ctx->dim && e == hipSuccess; a++) {
-            char *dstp = a == 0 ? (char *)phi : (char *)grad + size_t(a - 1) * pb;
-            e = hipMemcpy2DAsync(dstp, p, ws + size_t(a) * pb, p, w, rows, hipMemcpyDeviceToDevice, s);
+            const size_t o = size_t(a - 1) * pb;
+            e = hipMemcpy2DAsync(a == 0 ? to.phi : (char *)to.grad + o, p,
+                                 a == 0 ? from.phi : (char *)from.grad + o, p, w, rows,
+                                 hipMemcpyDeviceToDevice, s);
         }
     }
     return e;
+}
+
+// Launches planned for `steps` steps at step size dt.
+int64_t planned_launches(const gals_ctx *ctx, double dt, int64_t steps)
+{
+    const int most = multi_steps(ctx, dt);
+    return (steps + most - 1) / most;
+}
+
+// `steps` steps of (phi, grad) in place. An even number of launches from the
+// caller's buffers, or an odd one from the workspace's copy, ends in the
+// caller's buffers.
+hipError_t advance_in_place(const gals_ctx *ctx, void *phi, void *grad, double t0, double dt,
+                            int64_t steps, void *workspace, hipStream_t s)
+{
+    const size_t pb = size_t(ctx->g.plane) * elem_size(ctx);
+    char *ws = (char *)workspace;
+    int64_t left = planned_launches(ctx, dt, steps);
+    if ((left & 1) && left < steps) left++;
+    const Planes state = {phi, grad}, copy = {ws, ws + pb};
+    void *coltab, *rowtab;
+    table_slots(ctx, steps, workspace, coltab, rowtab);
+    hipError_t e = launch_prepare(ctx, coltab, rowtab, phi, grad, left & 1 ? ws : nullptr, s);
+    if (e != hipSuccess) return e;
+    return advance_core(ctx, state, left & 1 ? copy : state, state, t0, dt, 0, steps, steps, left,
+                        workspace, s);
 }
 
 template <typename T>
@@ -530,7 +558,7 @@ int gals_advance(gals_ctx *ctx, void *phi, void *grad, double t0, double dt, int
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "gals_advance: pending HIP error");
     hipStream_t s = (hipStream_t)stream;
-    e = advance_core(ctx, phi, grad, t0, dt, 0, steps, steps, true, workspace, s);
+    e = advance_in_place(ctx, phi, grad, t0, dt, steps, workspace, s);
     return e == hipSuccess ? GALS_OK : hip_fail(e, "gals_advance: launch");
 }
 
@@ -564,7 +592,7 @@ int gals_advance_noalloc(gals_ctx *ctx, void *phi, void *grad, double t0, double
     e = scratch_address(ctx->device, &ws);
     if (e != hipSuccess) return hip_fail(e, "gals_advance_noalloc: hipGetSymbolAddress");
     hipStream_t s = (hipStream_t)stream;
-    e = advance_core(ctx, phi, grad, t0, dt, 0, steps, steps, true, ws, s);
+    e = advance_in_place(ctx, phi, grad, t0, dt, steps, ws, s);
     return e == hipSuccess ? GALS_OK : hip_fail(e, "gals_advance_noalloc: launch");
 }
 
@@ -702,18 +730,6 @@ int check_adjoint_ctx(const gals_ctx *ctx, const char *what)
     return GALS_OK;
 }
 
-// Copy a state (phi plane, then dim gradient planes) to/from one contiguous
-// checkpoint slot.
-hipError_t copy_state(const gals_ctx *ctx, void *dphi, void *dgrad, const void *sphi,
-                      const void *sgrad, hipStream_t s)
-{
-    const size_t pb = size_t(ctx->g.plane) * elem_size(ctx);
-    hipError_t e = hipMemcpyAsync(dphi, sphi, pb, hipMemcpyDeviceToDevice, s);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(dgrad, sgrad, pb * size_t(ctx->dim), hipMemcpyDeviceToDevice, s);
-    return e;
-}
-
 }  // namespace
 
 extern "C" {
@@ -762,12 +778,21 @@ int gals_advance_save(gals_ctx *ctx, void *phi, void *grad, double t0, double dt
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "gals_advance_save: pending HIP error");
     hipStream_t s = (hipStream_t)stream;
-    for (int64_t k = 0; k < nsegments(steps, every) && e == hipSuccess; k++) {
-        char *slot = (char *)ckpt + size_t(k) * seg_state_bytes(ctx);
-        e = copy_state(ctx, slot, slot + pb, phi, grad, s);
+    // the first slot takes a copy; each later one is written by the last step
+    // of the segment before it and read by the first of its own
+    const Planes state = {phi, grad};
+    auto slot = [&](int64_t k) {
+        char *q = (char *)ckpt + size_t(k) * seg_state_bytes(ctx);
+        return Planes{q, q + pb};
+    };
+    const int64_t nseg = nsegments(steps, every);
+    void *coltab, *rowtab;
+    table_slots(ctx, steps, workspace, coltab, rowtab);
+    e = launch_prepare(ctx, coltab, rowtab, phi, grad, slot(0).phi, s);
+    for (int64_t k = 0; k < nseg && e == hipSuccess; k++) {
         const int64_t n0 = k * every, n1 = n0 + every < steps ? n0 + every : steps;
-        if (e == hipSuccess)
-            e = advance_core(ctx, phi, grad, t0, dt, n0, n1, steps, k == 0, workspace, s);
+        e = advance_core(ctx, state, slot(k), k + 1 < nseg ? slot(k + 1) : state, t0, dt, n0, n1,
+                         steps, planned_launches(ctx, dt, n1 - n0), workspace, s);
     }
     return e == hipSuccess ? GALS_OK : hip_fail(e, "gals_advance_save: launch");
 }
@@ -820,13 +845,15 @@ int gals_adjoint(gals_ctx *ctx, const void *ckpt, size_t ckpt_bytes, double t0, 
     if (e == hipSuccess) e = launch_zero(lamB, 3 * ctx->g.plane, s);
     for (int64_t k = nsegments(steps, every) - 1; k >= 0 && e == hipSuccess; k--) {
         const int64_t n0 = k * every, len = n0 + every < steps ? every : steps - n0;
-        // recompute the states of this segment from its checkpoint
+        // recompute the states of this segment from its checkpoint, which is
+        // the first of them
         const char *slot = (const char *)ckpt + size_t(k) * sb;
-        e = copy_state(ctx, seg, seg + pb, slot, slot + pb, s);
+        auto at = [&](int64_t q) -> const char * { return q ? seg + size_t(q) * sb : slot; };
         const void *coltab_c = coltab, *rowtab_c = rowtab;
         for (int64_t q = 1; q < len && e == hipSuccess; q++) {
             const double t = t0 + double(n0 + q - 1) * dt;
-            char *src = seg + size_t(q - 1) * sb, *dst = seg + size_t(q) * sb;
+            const char *src = at(q - 1);
+            char *dst = seg + size_t(q) * sb;
             e = launch_step(ctx, src, src + pb, dst, dst + pb, dt,
                             time_factor(ctx->period, t + dt), time_factor(ctx->period, t),
                             time_factor(ctx->period, t + 0.5 * dt), coltab_c, rowtab_c, s);
@@ -834,7 +861,7 @@ int gals_adjoint(gals_ctx *ctx, const void *ckpt, size_t ckpt_bytes, double t0, 
         // reverse sweep over the segment
         for (int64_t q = len - 1; q >= 0 && e == hipSuccess; q--) {
             const double t = t0 + double(n0 + q) * dt;
-            const char *u = seg + size_t(q) * sb;
+            const char *u = at(q);
             e = launch_adjoint_step(ctx, u, u + pb, lamA, lamB, true, part, dt,
                                     time_factor(ctx->period, t + dt), time_factor(ctx->period, t),
                                     time_factor(ctx->period, t + 0.5 * dt), coltab, rowtab, s);
