@@ -470,13 +470,18 @@ __device__ __forceinline__ void stage_vecpot(const Vel<T> &p, T (*tab)[kBlock], 
     modes_at<T, LDS>(p, tab, sx, cx, sy, cy, sz, cz, T(1), w, R);
 }
 
-// At least five waves per SIMD for the superconsistent kernel in FP32, three in
-// FP64 (150 VGPRs; at the compiler's choice of 170 two waves, 480 against 375 us
-// for two steps of 141 x 131 x 121 nodes); the Heun kernels need more registers
-// and keep the compiler's choice.
+// Waves per SIMD of the superconsistent kernel: six in FP32 (77 VGPRs; five
+// with 81 by the compiler's choice, 555 against 539 us per 257^3 step), five
+// with cell-based cross derivatives (six spill 14 VGPRs), three in FP64 (150
+// VGPRs; at the compiler's choice of 170 two waves, 480 against 375 us for two
+// steps of 141 x 131 x 121 nodes); the Heun kernels need more registers and
+// keep the compiler's choice.
 template <typename T, int MIX, bool SHIFT, int PSI>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
-    PSI != GALS_PSI_SUPERCONSISTENT ? 1 : sizeof(T) == 4 ? 5 : 3))) void k_step3d_vecpot(
+    PSI != GALS_PSI_SUPERCONSISTENT ? 1
+    : sizeof(T) != 4                ? 3
+    : MIX == GALS_MIXED_CELL        ? 5
+                                    : 6))) void k_step3d_vecpot(
     Geom g, Vel<T> p, Stage<T> st,
                                                           double dt, const T *__restrict__ tab,
                                                           const T *__restrict__ phi,
