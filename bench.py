@@ -84,11 +84,11 @@ BYTES_PER_NODE = 24  # FP32 state: 3 planes read once + 3 planes written once
 VARIANT_B_FLOPS_PER_NODE = ALG_FLOPS_PER_NODE - 8 + 28
 # FP32 3D step, 6-mode vector potential, central cross derivatives, as the
 # hardware counts it (SQ_INSTS_VALU_FLOPS_FP32 and _FP64, FMA = 2). Of these,
-# as formulated: velocity and Jacobian at the node from the per-axis tables 390
-# and at the two off-node stages 426 each, stage offsets and displacement 30,
+# as formulated: velocity and Jacobian at the node from the per-axis tables 366
+# and at the two off-node stages 402 each, stage offsets and displacement 30,
 # Jacobian chain 180, foot and split 30, gradient update 18; the rest is the
 # tricubic by combined stencil weights.
-FLOPS_PER_NODE_3D = 1948
+FLOPS_PER_NODE_3D = 1879
 BYTES_PER_NODE_3D = 32  # FP32 state: 4 planes read once + 4 planes written once
 # Bandwidth probe (rigid rotation, the cheapest field). The three stages of an
 # affine field compose to one affine map that the host forms once per step,
