@@ -170,8 +170,9 @@ int gals_set_psi_update(gals_ctx *ctx, int mode);
  * The flow enters through face a where its inward normal component exceeds
  * 1e-6 max(|v|, h_a / dt), so a face that is a streamline (a no-penetration
  * wall) or a stagnation point takes no data whatever the rounding of v.
- * The caller keeps the arrays alive while they are set. EINVAL for a
- * context of another boundary treatment. */
+ * The arrays may be the advanced state itself (inflow values held): one step
+ * then takes the values of its start. The caller keeps the arrays alive while
+ * they are set. EINVAL for a context of another boundary treatment. */
 int gals_set_inflow_data(gals_ctx *ctx, const void *phi_b, const void *grad_b,
                          const void *phit_b);
 

@@ -62,8 +62,8 @@ static InflowData<T> inflow_data(const gals_ctx *ctx)
 
 template <typename T, int D, int KIND>
 __device__ __forceinline__ void inflow_node(const Geom &g, const Vel<T> &p, T c, double dt,
-                                            const int *ijk, const InflowData<T> &b,
-                                            T *__restrict__ phi, T *__restrict__ grad)
+                                            const int *ijk, const InflowData<T> &b, T *phi,
+                                            T *grad)
 {
     double x[D];
 #pragma unroll

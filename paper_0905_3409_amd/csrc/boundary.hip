@@ -48,9 +48,10 @@ __device__ __forceinline__ bool boundary_node(const Geom &g, int64_t id, int *ij
 
 template <typename T, int D, int KIND>
 __global__ __launch_bounds__(kBlock) void k_inflow(Geom g, Vel<T> p, T c, double dt,
-                                                   int64_t count, InflowData<T> b,
-                                                   T *__restrict__ phi, T *__restrict__ grad)
+                                                   int64_t count, InflowData<T> b, T *phi,
+                                                   T *grad)
 {
+    // phi and grad may hold the data themselves
     const int64_t id = int64_t(blockIdx.x) * kBlock + threadIdx.x;
     int ijk[3] = {0, 0, 0};
     if (id >= count || !boundary_node<D>(g, id, ijk)) return;
@@ -72,8 +73,13 @@ __global__ __launch_bounds__(kBlock) void k_face(Geom g, Vel<T> p, Stage<T> st, 
 // ---------------------------------------------------------------------------
 // Launchers.
 // ---------------------------------------------------------------------------
-// The vortex and the 1D-like field are not listed: their step kernel (k_step2d)
-// treats its boundary nodes itself.
+// The vortex and the 1D-like field come here only with data that lie in the
+// state the step writes: their step kernel (k_step2d) treats its boundary nodes
+// itself otherwise.
+#define GALS_INFLOW_KINDS(X)                                                                      \
+    GALS_BOUNDARY_KINDS(X)                                                                        \
+    X(2, GALS_VEL_VORTEX)                                                                         \
+    X(2, GALS_VEL_PSEUDO1D)
 #define GALS_BOUNDARY_KINDS(X)                                                                    \
     X(2, GALS_VEL_AFFINE)                                                                         \
     X(2, GALS_VEL_STREAM_SIN)                                                                     \
@@ -96,7 +102,7 @@ static hipError_t inflow_typed(const gals_ctx *ctx, const Vel<T> &p, void *phi, 
                            ph, gr);                                                               \
         break;
     switch (ctx->dim * 16 + ctx->vel_kind) {
-        GALS_BOUNDARY_KINDS(GALS_INFLOW)
+        GALS_INFLOW_KINDS(GALS_INFLOW)
     default:
         return hipErrorInvalidValue;
     }

@@ -14,6 +14,23 @@ using namespace gals;
 
 namespace {
 thread_local char g_err[512] = "";
+
+bool overlap(const void *a, size_t na, const void *b, size_t nb)
+{
+    const char *pa = (const char *)a, *pb = (const char *)b;
+    return pa < pb + nb && pb < pa + na;
+}
+}  // namespace
+
+bool gals::inflow_data_in(const gals_ctx *ctx, const void *phi, const void *grad)
+{
+    if (!ctx->inflow) return false;
+    const size_t pb = size_t(ctx->g.plane) * (ctx->prec == GALS_F32 ? 4 : 8), d = size_t(ctx->dim);
+    auto meets = [&](const void *data, size_t n) {
+        return overlap(data, n, phi, pb) || overlap(data, n, grad, d * pb);
+    };
+    return meets(ctx->inflow_phi, pb) || meets(ctx->inflow_grad, d * pb) ||
+           meets(ctx->inflow_phit, pb);
 }
 
 void gals::set_error_v(const char *fmt, va_list ap) { vsnprintf(g_err, sizeof(g_err), fmt, ap); }
@@ -64,12 +81,6 @@ size_t workspace_bytes(const gals_ctx *c)
 {
     const size_t axis = 2 * size_t(c->g.n[0] + c->g.n[1] + c->g.n[2]) * elem_size(c);
     return axistab_offset(c) + align256(axis);
-}
-
-bool overlap(const void *a, size_t na, const void *b, size_t nb)
-{
-    const char *pa = (const char *)a, *pb = (const char *)b;
-    return pa < pb + nb && pb < pa + na;
 }
 
 bool aligned(const void *p, size_t a) { return (uintptr_t(p) % a) == 0; }
@@ -190,6 +201,19 @@ int64_t planned_launches(const gals_ctx *ctx, double dt, int64_t steps)
     return (steps + most - 1) / most;
 }
 
+// As advance_in_place for inflow data that lie in the state itself: every step
+// starts with the data of its own start, or, on the way back from the workspace,
+// keeps what it computed. So the steps go from the caller's buffers to the
+// workspace and back, and the result of an odd count is copied.
+hipError_t advance_own_data(const gals_ctx *ctx, void *phi, void *grad, double t0, double dt,
+                            int64_t n_begin, int64_t n_end, int64_t steps, void *workspace,
+                            hipStream_t s)
+{
+    const Planes state = {phi, grad};
+    return advance_core(ctx, state, state, state, t0, dt, n_begin, n_end, steps, n_end - n_begin,
+                        workspace, s);
+}
+
 // `steps` steps of (phi, grad) in place. An even number of launches from the
 // caller's buffers, or an odd one from the workspace's copy, ends in the
 // caller's buffers.
@@ -203,6 +227,12 @@ hipError_t advance_in_place(const gals_ctx *ctx, void *phi, void *grad, double t
     const Planes state = {phi, grad}, copy = {ws, ws + pb};
     void *coltab, *rowtab;
     table_slots(ctx, steps, workspace, coltab, rowtab);
+    if (inflow_data_in(ctx, phi, grad)) {
+        const hipError_t e = launch_prepare(ctx, coltab, rowtab, phi, grad, nullptr, s);
+        return e != hipSuccess ? e
+                               : advance_own_data(ctx, phi, grad, t0, dt, 0, steps, steps,
+                                                  workspace, s);
+    }
     hipError_t e = launch_prepare(ctx, coltab, rowtab, phi, grad, left & 1 ? ws : nullptr, s);
     if (e != hipSuccess) return e;
     return advance_core(ctx, state, left & 1 ? copy : state, state, t0, dt, 0, steps, steps, left,
@@ -789,8 +819,15 @@ int gals_advance_save(gals_ctx *ctx, void *phi, void *grad, double t0, double dt
     void *coltab, *rowtab;
     table_slots(ctx, steps, workspace, coltab, rowtab);
     e = launch_prepare(ctx, coltab, rowtab, phi, grad, slot(0).phi, s);
+    const bool own_data = inflow_data_in(ctx, phi, grad);
     for (int64_t k = 0; k < nseg && e == hipSuccess; k++) {
         const int64_t n0 = k * every, n1 = n0 + every < steps ? n0 + every : steps;
+        if (own_data) {  // every slot takes a copy
+            if (k > 0) e = launch_prepare(ctx, nullptr, nullptr, phi, grad, slot(k).phi, s);
+            if (e == hipSuccess)
+                e = advance_own_data(ctx, phi, grad, t0, dt, n0, n1, steps, workspace, s);
+            continue;
+        }
         e = advance_core(ctx, state, slot(k), k + 1 < nseg ? slot(k + 1) : state, t0, dt, n0, n1,
                          steps, planned_launches(ctx, dt, n1 - n0), workspace, s);
     }

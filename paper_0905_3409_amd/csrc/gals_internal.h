@@ -242,6 +242,11 @@ hipError_t launch_multi_step(const gals_ctx *ctx, int k, const double (*c)[3], c
 hipError_t launch_prepare(const gals_ctx *ctx, void *coltab, void *rowtab, const void *phi,
                           const void *grad, void *copy, hipStream_t s);
 
+// Whether the context's Dirichlet inflow data lie in the state at (phi, grad):
+// a step that writes there takes its conditions in a launch of its own, after
+// all of its nodes (gals_api.hip).
+bool inflow_data_in(const gals_ctx *ctx, const void *phi, const void *grad);
+
 // Inflow boundary conditions after a step of size dt (boundary.hip):
 // Dirichlet data at time factor c, and homogeneous Neumann inflow by the face
 // scheme from the state before the step (sphi, sgrad) into the stepped one.

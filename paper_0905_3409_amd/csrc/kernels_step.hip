@@ -706,7 +706,8 @@ static hipError_t launch_typed(const gals_ctx *ctx, const Vel<T> &p, const void 
     }
     if (ctx->dim == 2) {
         if constexpr (KIND == GALS_VEL_VORTEX || KIND == GALS_VEL_PSEUDO1D) {
-            auto kern = ctx->inflow ? k_step2d<T, KIND, MIX, PSI, kBcInflow>
+            const bool in_step = ctx->inflow && !inflow_data_in(ctx, phi_o, grad_o);
+            auto kern = in_step     ? k_step2d<T, KIND, MIX, PSI, kBcInflow>
                         : ctx->face ? k_step2d<T, KIND, MIX, PSI, kBcFace>
                                     : k_step2d<T, KIND, MIX, PSI, kBcNone>;
             hipLaunchKernelGGL(kern, dim3(blocks), dim3(kBlock), 0, s, ctx->g, p, st, dt,
@@ -772,8 +773,10 @@ hipError_t launch_step(const gals_ctx *ctx, const void *phi, const void *grad, v
                    : launch_kind<double, MIX, PSI>(ctx, ctx->vd, phi, grad, phi_o, grad_o, dt, c1,
                                                    c2, c3, coltab, s);
     });
-    // k_step2d has treated its boundary nodes
-    if (ctx->vel_kind == GALS_VEL_VORTEX || ctx->vel_kind == GALS_VEL_PSEUDO1D) return e;
+    // k_step2d has treated its boundary nodes, except with data in its own output
+    if ((ctx->vel_kind == GALS_VEL_VORTEX || ctx->vel_kind == GALS_VEL_PSEUDO1D) &&
+        !inflow_data_in(ctx, phi_o, grad_o))
+        return e;
     if (e == hipSuccess && ctx->inflow) e = launch_inflow(ctx, phi_o, grad_o, c1, dt, s);
     if (e == hipSuccess && ctx->face)
         e = launch_face(ctx, phi, grad, phi_o, grad_o, dt, c1, c2, c3, s);
