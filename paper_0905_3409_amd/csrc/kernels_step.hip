@@ -542,20 +542,53 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
 // (TAB), and, when an odd number of launches follows, the state's copy in the
 // workspace that the first of them reads, so that the last one ends in the
 // caller's buffers. The first `tab_blocks` blocks build entries, the others copy
-// whole planes, padding included (the copy's padding is never read), 16 bytes a
-// thread at a time where the caller's planes allow. (A table launch before and
-// one pitched copy per plane after the last step: 24 us per one-step call on 501 x
-// 380 FP32 nodes, 81 on 2049^2, 303 on 4097 x 4096; 17, 62 and 244 with this.)
+// the nodes of every row, without the padding, 16 bytes a thread at a time where
+// the caller's planes allow. (A table launch before and one pitched copy per
+// plane after the last step: 24 us per one-step call on 501 x 380 FP32 nodes, 81
+// on 2049^2, 303 on 4097 x 4096; 17, 62 and 244 with this. Rows of three nodes
+// with their padding are 21 times the bytes: a step of 3 x 401 x 401 FP64 nodes 194
+// us with whole planes, 68 with this.)
 // ---------------------------------------------------------------------------
 enum { kTabNone = 0, kTabStream = 1, kTabAxis = 2 };
 
-template <typename V>
-__device__ __forceinline__ void copy_span(const void *__restrict__ src, void *__restrict__ dst,
-                                          int64_t bytes, int64_t id, int64_t stride)
+// How the copy's work items cut a row: `per` items of `width` elements, the last
+// of them with what is left of the row; magic = floor(2^32 / per).
+struct RowCut {
+    unsigned per, width, magic;
+};
+
+template <typename T>
+__device__ __forceinline__ void copy_rows(const Geom &g, const RowCut &cut,
+                                          const T *__restrict__ phi, const T *__restrict__ grad,
+                                          T *__restrict__ copy, unsigned id, unsigned stride)
 {
-    const V *s = static_cast<const V *>(src);
-    V *d = static_cast<V *>(dst);
-    for (int64_t k = id; k < bytes / int64_t(sizeof(V)); k += stride) d[k] = s[k];
+    // at most 2^31 items (a plane is under 2 GiB), stride at most 2^21: no index wraps
+    const unsigned rows = unsigned(g.n[1]) * unsigned(g.n[2]);
+    const unsigned items = cut.per * rows * unsigned(1 + g.dim);
+    for (; id < items; id += stride) {
+        unsigned v, r = udiv_magic(id, cut.per, cut.magic, v), a = 0;
+        while (r >= rows) {
+            r -= rows;
+            a++;
+        }
+        const int64_t o = int64_t(r) * g.pitch + int64_t(v) * cut.width;
+        const T *s = a == 0 ? phi + o : grad + int64_t(a - 1) * g.plane + o;
+        T *d = copy + int64_t(a) * g.plane + o;
+        const unsigned left = unsigned(g.n[0]) - v * cut.width;
+        if (cut.width > 1u && left >= cut.width) {
+            *reinterpret_cast<uint4 *>(d) = *reinterpret_cast<const uint4 *>(s);
+            continue;
+        }
+        // the rest of a row, its loads issued together; one element where not wide
+        const unsigned n = left < cut.width ? left : cut.width;
+        T t[3];
+#pragma unroll
+        for (unsigned k = 0; k < 3u; k++)
+            if (k < n) t[k] = s[k];
+#pragma unroll
+        for (unsigned k = 0; k < 3u; k++)
+            if (k < n) d[k] = t[k];
+    }
 }
 
 template <typename T, int TAB>
@@ -563,7 +596,7 @@ __global__ __launch_bounds__(kBlock) void k_prepare(Geom g, Vel<double> p, unsig
                                                     T *__restrict__ tab0, T *__restrict__ tab1,
                                                     const T *__restrict__ phi,
                                                     const T *__restrict__ grad,
-                                                    T *__restrict__ copy, int wide)
+                                                    T *__restrict__ copy, RowCut cut)
 {
     if (blockIdx.x < tab_blocks) {
         const int id = int(blockIdx.x) * kBlock + int(threadIdx.x);
@@ -580,16 +613,8 @@ __global__ __launch_bounds__(kBlock) void k_prepare(Geom g, Vel<double> p, unsig
         }
         return;
     }
-    const int64_t id = int64_t(blockIdx.x - tab_blocks) * kBlock + threadIdx.x;
-    const int64_t stride = int64_t(gridDim.x - tab_blocks) * kBlock;
-    const int64_t pb = g.plane * int64_t(sizeof(T));  // a multiple of 256 bytes
-    if (wide) {
-        copy_span<uint4>(phi, copy, pb, id, stride);
-        copy_span<uint4>(grad, copy + g.plane, pb * g.dim, id, stride);
-    } else {
-        copy_span<T>(phi, copy, pb, id, stride);
-        copy_span<T>(grad, copy + g.plane, pb * g.dim, id, stride);
-    }
+    copy_rows(g, cut, phi, grad, copy, (blockIdx.x - tab_blocks) * unsigned(kBlock) + threadIdx.x,
+              (gridDim.x - tab_blocks) * unsigned(kBlock));
 }
 
 template <typename T>
@@ -600,18 +625,23 @@ static hipError_t prepare_typed(const gals_ctx *ctx, int tab, void *tab0, void *
     const int64_t entries = tab == kTabStream ? stream_table_threads(g)
                             : tab == kTabAxis ? int64_t(g.n[0]) + g.n[1] + g.n[2] : 0;
     const unsigned tb = unsigned((entries + kBlock - 1) / kBlock);
+    // rows start at multiples of 64 elements, and the copy at a multiple of 256 bytes
     const bool wide = (uintptr_t(phi) | uintptr_t(grad)) % 16 == 0;
+    RowCut cut;
+    cut.width = wide ? unsigned(16 / sizeof(T)) : 1u;
+    cut.per = (unsigned(g.n[0]) + cut.width - 1u) / cut.width;
+    cut.magic = cut.per > 1u ? unsigned((uint64_t(1) << 32) / cut.per) : 0xFFFFFFFFu;
     int64_t cb = 0;
     if (copy) {
-        const int64_t spans = g.plane * (1 + g.dim) * int64_t(sizeof(T)) / 16;
-        cb = (spans + kBlock - 1) / kBlock;
+        const int64_t items = int64_t(cut.per) * g.n[1] * g.n[2] * (1 + g.dim);
+        cb = (items + kBlock - 1) / kBlock;
         if (cb > 8192) cb = 8192;
     }
     if (tb + cb == 0) return hipSuccess;
     auto kern = tab == kTabStream ? k_prepare<T, kTabStream>
                 : tab == kTabAxis ? k_prepare<T, kTabAxis> : k_prepare<T, kTabNone>;
     hipLaunchKernelGGL(kern, dim3(tb + unsigned(cb)), dim3(kBlock), 0, s, g, ctx->vd, tb, (T *)tab0,
-                       (T *)tab1, (const T *)phi, (const T *)grad, (T *)copy, int(wide));
+                       (T *)tab1, (const T *)phi, (const T *)grad, (T *)copy, cut);
     return hipGetLastError();
 }
 
