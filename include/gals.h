@@ -23,8 +23,10 @@
  *   `pitch` elements, x fastest: element (i,j,k) at i + pitch*(j + n[1]*k).
  *   pitch = n[0] rounded up to a multiple of 64; `plane_stride` =
  *   pitch*n[1](*n[2]) elements. `phi` points to one plane; `grad` to dim
- *   planes at grad + a*plane_stride (psi_x, psi_y[, psi_z]). Padding
- *   elements are never read or written. Device pointers must be aligned to
+ *   planes at grad + a*plane_stride (psi_x, psi_y[, psi_z]). The padding of
+ *   a state's rows is never written and what it holds never affects a result;
+ *   a row's padding may be read together with its last nodes, but nothing past
+ *   the last node of a plane is accessed. Device pointers must be aligned to
  *   their element size.
  * Streams: `stream` is a hipStream_t passed as void* (NULL = the null
  *   stream). Calls marked "async" only enqueue work on it.

@@ -390,8 +390,7 @@ int gals_batch_create(gals_batch **out, int64_t nprob, const int64_t *ncell, con
         }
         g.nodes = int64_t(g.n[0]) * g.n[1];
         geom_finish(g);
-        g.pitch = round_up(g.n[0], 64);
-        g.plane = g.pitch * g.n[1];
+        geom_layout(g);
         if (g.plane * esz >= (int64_t(1) << 31)) {
             delete b;
             return bfail(GALS_EINVAL, "gals_batch_create: problem %lld plane of 2 GiB or more",

@@ -41,6 +41,7 @@ struct Geom {
     double inv_h[3];
     int64_t pitch;   // row pitch in elements
     int64_t plane;   // plane stride in elements
+    int64_t span;    // elements of a plane up to and including its last node
     int64_t nodes;   // n[0]*n[1]*n[2]
     // derived by geom_finish, so that kernels need no per-wave conversions:
     double ncd[3];   // nc as double
@@ -88,6 +89,14 @@ inline void geom_finish(Geom &g)
     g.tiles_x_magic = g.tiles_x > 1 ? unsigned((uint64_t(1) << 32) / g.tiles_x) : 0xFFFFFFFFu;
     for (int a = 0; a < 3; a++)
         g.n_magic[a] = g.n[a] > 1 ? unsigned((uint64_t(1) << 32) / unsigned(g.n[a])) : 0xFFFFFFFFu;
+}
+
+// Fill the layout fields of a Geom whose n is set.
+inline void geom_layout(Geom &g)
+{
+    g.pitch = (int64_t(g.n[0]) + 63) / 64 * 64;
+    g.plane = g.pitch * g.n[1] * g.n[2];
+    g.span = g.plane - g.pitch + g.n[0];
 }
 
 // Threads that build a grid's stream-function tables (stream_table_entry).

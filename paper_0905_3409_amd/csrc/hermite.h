@@ -247,10 +247,11 @@ __device__ __forceinline__ void split(const Geom &g, const double *X, int *cell,
 }
 
 // ---------------------------------------------------------------------------
-// Raw buffer loads: one descriptor per plane (base, size in bytes), 32-bit
-// element offsets, reads outside the plane return 0. The host keeps every
-// plane below 2 GiB, so its size in bytes and every byte offset into it fit a
-// signed 32-bit integer.
+// Raw buffer loads: one descriptor per plane (base, bytes up to its last node,
+// g.span), 32-bit element offsets; what lies beyond is not accessed and reads as
+// 0, word by word, so a wide load may hang over the last node. The host keeps
+// every plane below 2 GiB, so its size in bytes and every byte offset into it
+// fit a signed 32-bit integer.
 // ---------------------------------------------------------------------------
 typedef __amdgpu_buffer_rsrc_t Rsrc;
 
@@ -722,8 +723,9 @@ __device__ __forceinline__ void tricubic_central(const Geom &g, Rsrc rphi, Rsrc 
     // A row's four x nodes are one window of wide loads: c - 1 .. c + 2, or
     // 0 .. 3 at the first cell, whose weights move down by one. The window's
     // last value belongs to no stencil at the first cell and lies past the row
-    // at the last one (in the padding, the next row, or past the plane, where
-    // a buffer load gives 0): it is replaced by 0 there, whatever it holds.
+    // at the last one (in the row's padding, the next row, or past the plane's
+    // last node, where a buffer load gives 0): it is replaced by 0 there,
+    // whatever it holds.
     // Rows past the grid repeat their neighbour with weight 0.
     const unsigned xm = xlo ? 0u : 1u;
     const bool xedge = xlo || xhi;

@@ -58,7 +58,7 @@ __global__ __launch_bounds__(kBlock) void k_step2d(Geom g, Vel<T> p, Stage<T> st
     const T xi[2] = {T(xid[0]), T(xid[1])};
     if constexpr (kFold2d<T, MIX>) pin4(J);
     T H, Hx, Hy;
-    bicubic<T, MIX>(g, plane_rsrc(phi, g.plane), plane_rsrc(gx, g.plane), plane_rsrc(gy, g.plane),
+    bicubic<T, MIX>(g, plane_rsrc(phi, g.span), plane_rsrc(gx, g.span), plane_rsrc(gy, g.span),
                     cell, xi, H, Hx, Hy);
     if (out & 1u) Hx = T(0);
     if (out & 2u) Hy = T(0);
@@ -123,8 +123,8 @@ struct TileStager {
     __device__ __forceinline__ void load(const Geom &g, const T *phi, const T *gx, const T *gy,
                                          int cx0, int ry0)
     {
-        const Rsrc r0 = plane_rsrc(phi, g.plane), r1 = plane_rsrc(gx, g.plane),
-                   r2 = plane_rsrc(gy, g.plane);
+        const Rsrc r0 = plane_rsrc(phi, g.span), r1 = plane_rsrc(gx, g.span),
+                   r2 = plane_rsrc(gy, g.span);
         const unsigned past = unsigned(g.plane);
         const int tid = int(threadIdx.y) * 64 + int(threadIdx.x);
 #pragma unroll
@@ -252,8 +252,8 @@ __global__ __launch_bounds__(kBlock) void k_step2d_affine(Geom g, TileGrid tg, A
             finish(H, Hx, Hy);
         } else {
             T H, Hx, Hy;
-            bicubic<T, MIX, false>(g, plane_rsrc(phi, g.plane), plane_rsrc(gx, g.plane),
-                                   plane_rsrc(gy, g.plane), cell[r], xi[r], H, Hx, Hy);
+            bicubic<T, MIX, false>(g, plane_rsrc(phi, g.span), plane_rsrc(gx, g.span),
+                                   plane_rsrc(gy, g.span), cell[r], xi[r], H, Hx, Hy);
             finish(H, Hx, Hy);
         }
     }
@@ -321,8 +321,8 @@ __global__ __launch_bounds__(kBlock) void k_step3d_affine(Geom g, AffineMap<T> a
     split_cells<T, 3>(g, sc, cell, xi, outb);
     const T *gx = grad, *gy = grad + g.plane, *gz = grad + 2 * g.plane;
     T H, G[3];
-    tricubic<T, MIX>(g, plane_rsrc(phi, g.plane), plane_rsrc(gx, g.plane), plane_rsrc(gy, g.plane),
-                     plane_rsrc(gz, g.plane), cell, xi, H, G);
+    tricubic<T, MIX>(g, plane_rsrc(phi, g.span), plane_rsrc(gx, g.span), plane_rsrc(gy, g.span),
+                     plane_rsrc(gz, g.span), cell, xi, H, G);
     T Hx = G[0], Hy = G[1], Hz = G[2];
     if (outb[0]) Hx = T(0);
     if (outb[1]) Hy = T(0);
@@ -361,8 +361,8 @@ __device__ __forceinline__ void finish3d(const Geom &g, const Vel<T> &p, const S
     split<3>(g, X, cell, xid);
     const T xi[3] = {T(xid[0]), T(xid[1]), T(xid[2])};
     T H, gradH[3];
-    tricubic<T, MIX>(g, plane_rsrc(phi, g.plane), plane_rsrc(gx, g.plane), plane_rsrc(gy, g.plane),
-                     plane_rsrc(gz, g.plane), cell, xi, H, gradH);
+    tricubic<T, MIX>(g, plane_rsrc(phi, g.span), plane_rsrc(gx, g.span), plane_rsrc(gy, g.span),
+                     plane_rsrc(gz, g.span), cell, xi, H, gradH);
     T Hx = gradH[0], Hy = gradH[1], Hz = gradH[2];
     if (out & 1u) Hx = T(0);
     if (out & 2u) Hy = T(0);
