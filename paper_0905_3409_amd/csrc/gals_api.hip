@@ -104,16 +104,16 @@ struct DeviceGuard {
 double time_factor(double period, double t) { return period > 0.0 ? cos(M_PI * t / period) : 1.0; }
 
 // Whether the steps of an advance of `steps` steps read the per-axis sin/cos
-// table. The vector potential always does. The vortex in FP64 and the 3D
-// deformation field take it from 2^21 node-steps on, else their kernels form
+// table. The vector potential always does. The vortex and the 3D deformation
+// field take it in FP64 from 2^21 node-steps on, else their kernels form
 // the node's own angles: the table saves them about 1 us per 2^20 node-steps
 // and its launch costs 2.5 to 3 us (64^2 vortex, 8 steps 40 us without, 43
 // with; 101^3 deformation field, 8 steps 307 without, 299 with).
 bool axis_tables(const gals_ctx *ctx, int64_t steps)
 {
     if (ctx->vel_kind == GALS_VEL_VECPOT_SIN) return true;
-    const bool trig = ctx->vel_kind == GALS_VEL_LEVEQUE3D ||
-                      (ctx->vel_kind == GALS_VEL_VORTEX && ctx->prec == GALS_F64);
+    const bool trig = ctx->prec == GALS_F64 && (ctx->vel_kind == GALS_VEL_LEVEQUE3D ||
+                                                ctx->vel_kind == GALS_VEL_VORTEX);
     return trig && double(ctx->g.nodes) * double(steps) >= double(1 << 21);
 }
 

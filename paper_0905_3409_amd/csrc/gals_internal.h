@@ -244,9 +244,9 @@ hipError_t launch_multi_step(const gals_ctx *ctx, int k, const double (*c)[3], c
                              const void *grad, void *phi_o, void *grad_o, double dt,
                              const void *coltab, const void *rowtab, hipStream_t s, int *took);
 // One launch before the first step (kernels_step.hip): the field's tables into
-// coltab and rowtab (per-column / per-row stream-function tables; for trig
-// fields and vector potentials sin(pi x), cos(pi x) per node of each axis, x,
-// then y, then z, into coltab; none if coltab is NULL), and the state's copy
+// coltab and rowtab (per-column / per-row stream-function tables; sin and cos per
+// node of each axis, x, then y, then z, into coltab, of pi x for vector
+// potentials, of 2 pi x for trig fields; none if coltab is NULL), and the state's copy
 // (1 + dim planes) into `copy` unless that is NULL.
 hipError_t launch_prepare(const gals_ctx *ctx, void *coltab, void *rowtab, const void *phi,
                           const void *grad, void *copy, hipStream_t s);

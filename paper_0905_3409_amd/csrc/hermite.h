@@ -98,66 +98,95 @@ __device__ __forceinline__ void trace(const Vel<T> &p, const Stage<T> &st, doubl
     }
 }
 
-// The same trace for a trig field (kTrigField): sin and cos of the node's
-// angles once, from the per-axis table (tab, entries ti[a]) or, without one,
-// from sincospi, and at the two off-node stages by angle addition while every
-// offset is in the series' range, sincospi beyond. w_k, R_k are the stage
-// fields without the time factor (see Stage). An FP64 sincospi costs about 45
-// instructions, a shifted pair 19: 101^3 FP64 deformation field 40.5 -> 36 us
-// per step, 513^2 FP64 vortex 8.3 -> 7 us, 151 x 152 x 141 FP32 deformation
-// field 65 -> 57 us.
+// The chain with the weighted terms summed before they leave the identity: one
+// rounding at the size of 1 in place of three, as in jacobian_chain.
+template <typename T, int D>
+__device__ __forceinline__ void jacobian_chain_s(const T *R0, const T *R1, const T *R2,
+                                                 const Stage<T> &st, T *J)
+{
+    T J1[D * D], P1[D * D], J2[D * D], P2[D * D];
+#pragma unroll
+    for (int k = 0; k < D * D; k++) J1[k] = T((k % (D + 1)) == 0) - st.e1 * R0[k];
+    matmul_acc<T, D>(R1, J1, P1);
+#pragma unroll
+    for (int k = 0; k < D * D; k++)
+        J2[k] = T((k % (D + 1)) == 0) - (st.q1 * R0[k] + st.q2 * P1[k]);
+    matmul_acc<T, D>(R2, J2, P2);
+#pragma unroll
+    for (int k = 0; k < D * D; k++)
+        J[k] = T((k % (D + 1)) == 0) - (st.f1 * R0[k] + st.f2 * P1[k] + st.f3 * P2[k]);
+}
+
+// The same trace for a trig field (kTrigField) in FP64: sin and cos of twice the
+// node's angles once, from the per-axis table (tab, entries ti[a]) or, without
+// one, from sincospi, and at the two off-node stages by angle addition while every
+// offset is in the series' range, sincospi beyond. An FP64 sincospi costs about 45
+// instructions, a shifted pair 22: 101^3 FP64 deformation field 40.5 -> 37 us per
+// step, 513^2 FP64 vortex 8.7 -> 7.4. The node's rounded sine enters all three
+// stages alike, so with sin and cos of the angles themselves the Jacobian's largest
+// error would be up to 1.4 times trace's at 3 cells a step on coarse grids; with
+// twice the angles foot and Jacobian are no further off than trace's. An FP32 state
+// keeps trace: angles added in FP32 raise the foot's largest error from 5.5e-7 to
+// 8.0e-7 cells and the Jacobian's from 7e-8 to 1.8e-7 at 3 cells a step on 151^3
+// nodes (57 us per step against 65).
+// w_k, R_k are the stage fields without the time factor (see Stage).
 template <typename T, int D, int KIND, bool CHAIN = true>
 __device__ __forceinline__ void trace_trig(const Stage<T> &st, const T *__restrict__ tab,
                                            const int64_t *ti, const double *x, double *X, T *J)
 {
+    static_assert(sizeof(T) == 8, "FP64 states only");
     T s0[D], c0[D];
-    if (tab) {
 #pragma unroll
-        for (int a = 0; a < D; a++) {
+    for (int a = 0; a < D; a++) {
+        if (tab) {
             s0[a] = tab[2 * ti[a]];
             c0[a] = tab[2 * ti[a] + 1];
-        }
-    } else {
-        // as the table is built, so that both give the same bits
-#pragma unroll
-        for (int a = 0; a < D; a++) {
-            double s, c;
-            sincospi(x[a], &s, &c);
-            s0[a] = T(s);
-            c0[a] = T(c);
+        } else {
+            sincospi(2.0 * x[a], &s0[a], &c0[a]);  // as the table is built
         }
     }
     auto stage = [&](const T *d, T *w, T *R) {
         T s[D], c[D];
         bool near = true;
 #pragma unroll
-        for (int a = 0; a < D; a++) near = near && fabs(d[a]) <= T(kShiftMaxWide<T> / kPi);
+        for (int a = 0; a < D; a++) near = near && fabs(d[a]) <= kShift2Max / (2.0 * kPi);
         if (near) {
 #pragma unroll
-            for (int a = 0; a < D; a++) shifted_sincos_wide(s0[a], c0[a], d[a], s[a], c[a]);
+            for (int a = 0; a < D; a++) shifted_sincos2(s0[a], c0[a], d[a], s[a], c[a]);
         } else {
 #pragma unroll
-            for (int a = 0; a < D; a++) sincospi_t(T(x[a] + double(d[a])), &s[a], &c[a]);
+            for (int a = 0; a < D; a++) sincospi(2.0 * (x[a] + d[a]), &s[a], &c[a]);
         }
-        trig_field<T, KIND>(s, c, T(1), w, R);
+        trig_field2<T, KIND, D>(s, c, T(1), w, R);
     };
-    T w0[D], R0[D * D], w1[D], R1[D * D], w2[D], R2[D * D], d1[D], d2[D];
-    trig_field<T, KIND>(s0, c0, T(1), w0, R0);  // at x, t + dt
+    T w0[D], R0[D * D], w1[D], R1[D * D], w2[D], R2[D * D], d[D];
+    trig_field2<T, KIND, D>(s0, c0, T(1), w0, R0);  // at x, t + dt
 #pragma unroll
-    for (int a = 0; a < D; a++) d1[a] = -st.e1 * w0[a];
-    stage(d1, w1, R1);  // at x1 = x + d1, t
+    for (int a = 0; a < D; a++) d[a] = -st.e1 * w0[a];
+    stage(d, w1, R1);  // at x + d, t
 #pragma unroll
-    for (int a = 0; a < D; a++) d2[a] = -(st.q1 * w0[a] + st.q2 * w1[a]);
-    stage(d2, w2, R2);  // at x2 = x + d2, t + dt/2
+    for (int a = 0; a < D; a++) d[a] = -(st.q1 * w0[a] + st.q2 * w1[a]);
+    stage(d, w2, R2);  // at x + d, t + dt/2
 #pragma unroll
-    for (int a = 0; a < D; a++)
-        X[a] = x[a] - double(st.f1 * w0[a] + st.f2 * w1[a] + st.f3 * w2[a]);
+    for (int a = 0; a < D; a++) X[a] = x[a] - (st.f1 * w0[a] + st.f2 * w1[a] + st.f3 * w2[a]);
     if constexpr (CHAIN) {
-        jacobian_chain_w<T, D>(R0, R1, R2, st, J);
+        jacobian_chain_s<T, D>(R0, R1, R2, st, J);
     } else {
 #pragma unroll
         for (int k = 0; k < D * D; k++) J[k] = st.c1 * R0[k];
     }
+}
+
+// The trace of a grid node: tab and ti as in trace_trig.
+template <typename T, int D, int KIND, bool CHAIN>
+__device__ __forceinline__ void trace_node(const Vel<T> &p, const Stage<T> &st, double dt,
+                                           const T *__restrict__ tab, const int64_t *ti,
+                                           const double *x, double *X, T *J)
+{
+    if constexpr (kTrigField<KIND> && sizeof(T) == 8)
+        trace_trig<T, D, KIND, CHAIN>(st, tab, ti, x, X, J);
+    else
+        trace<T, D, KIND, CHAIN>(p, st, dt, x, X, J);
 }
 
 // Heun's method for d psi/d tau = -grad v . psi (eq. cir_evolution_psi)

@@ -44,12 +44,8 @@ __global__ __launch_bounds__(kBlock) void k_step2d(Geom g, Vel<T> p, Stage<T> st
     const double x[2] = {node_coord(g.lo[0], i, g.h[0]), node_coord(g.lo[1], j, g.h[1])};
     double X[2];
     T J[4];  // superconsistent Jacobian, or (Heun) grad v at the node
-    if constexpr (kTrigField<KIND> && sizeof(T) == 8) {
-        const int64_t ti[2] = {i, int64_t(g.n[0]) + j};
-        trace_trig<T, 2, KIND, PSI == GALS_PSI_SUPERCONSISTENT>(st, tab, ti, x, X, J);
-    } else {
-        trace<T, 2, KIND, PSI == GALS_PSI_SUPERCONSISTENT>(p, st, dt, x, X, J);
-    }
+    const int64_t ti[2] = {i, int64_t(g.n[0]) + j};
+    trace_node<T, 2, KIND, PSI == GALS_PSI_SUPERCONSISTENT>(p, st, dt, tab, ti, x, X, J);
     const unsigned out = project_foot<2>(g, X);
 
     int cell[2];
@@ -386,13 +382,27 @@ __device__ __forceinline__ void finish3d(const Geom &g, const Vel<T> &p, const S
     }
 }
 
+// Waves per SIMD of the superconsistent 3D kernels. FP32: six for the vector
+// potential (77 VGPRs; five with 81 by the compiler's choice, 555 against 539 us
+// per 257^3 step), five with cell-based cross derivatives (six spill 14 VGPRs) and
+// for the deformation field (six spill 4, 151 x 152 x 141 nodes 67.3 against 64.8
+// us per step). FP64: three (vector potential 150 VGPRs; at the compiler's choice
+// of 170 two waves, 480 against 375 us for two steps of 141 x 131 x 121 nodes), also
+// with cell-based cross derivatives, where they spill 10 VGPRs (246 against 293
+// with two waves and no spill; deformation field the same at two and three). The
+// Heun kernels need more registers and keep the compiler's choice.
 template <typename T, int KIND, int MIX, int PSI>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
-    PSI != GALS_PSI_SUPERCONSISTENT ? 1 : sizeof(T) == 4 ? 5 : 3))) void k_step3d(Geom g, Vel<T> p, Stage<T> st, double dt,
-                                                   const T *__restrict__ tab,
-                                                   const T *__restrict__ phi,
-                                                   const T *__restrict__ grad,
-                                                   T *__restrict__ phi_o, T *__restrict__ grad_o)
+constexpr int kWaves3d = PSI != GALS_PSI_SUPERCONSISTENT                            ? 1
+                         : sizeof(T) != 4                                           ? 3
+                         : MIX == GALS_MIXED_CELL || KIND == GALS_VEL_LEVEQUE3D     ? 5
+                                                                                    : 6;
+
+template <typename T, int KIND, int MIX, int PSI>
+__global__ __launch_bounds__(kBlock)
+    __attribute__((amdgpu_waves_per_eu(kWaves3d<T, KIND, MIX, PSI>))) void k_step3d(
+        Geom g, Vel<T> p, Stage<T> st, double dt, const T *__restrict__ tab,
+        const T *__restrict__ phi, const T *__restrict__ grad, T *__restrict__ phi_o,
+        T *__restrict__ grad_o)
 {
     int i, j, k;
     if (!band_node3d(g, i, j, k)) return;
@@ -402,7 +412,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
     double X[3];
     T J[9];
     const int64_t ti[3] = {i, int64_t(g.n[0]) + j, int64_t(g.n[0]) + g.n[1] + k};
-    trace_trig<T, 3, KIND, PSI == GALS_PSI_SUPERCONSISTENT>(st, tab, ti, x, X, J);
+    trace_node<T, 3, KIND, PSI == GALS_PSI_SUPERCONSISTENT>(p, st, dt, tab, ti, x, X, J);
     finish3d<T, KIND, MIX, PSI>(g, p, st, dt, i, j, k, X, J, phi, grad, phi_o, grad_o);
 }
 
@@ -470,24 +480,13 @@ __device__ __forceinline__ void stage_vecpot(const Vel<T> &p, T (*tab)[kBlock], 
     modes_at<T, LDS>(p, tab, sx, cx, sy, cy, sz, cz, T(1), w, R);
 }
 
-// Waves per SIMD of the superconsistent kernel: six in FP32 (77 VGPRs; five
-// with 81 by the compiler's choice, 555 against 539 us per 257^3 step), five
-// with cell-based cross derivatives (six spill 14 VGPRs), three in FP64 (150
-// VGPRs; at the compiler's choice of 170 two waves, 480 against 375 us for two
-// steps of 141 x 131 x 121 nodes); the Heun kernels need more registers and
-// keep the compiler's choice.
 template <typename T, int MIX, bool SHIFT, int PSI>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
-    PSI != GALS_PSI_SUPERCONSISTENT ? 1
-    : sizeof(T) != 4                ? 3
-    : MIX == GALS_MIXED_CELL        ? 5
-                                    : 6))) void k_step3d_vecpot(
-    Geom g, Vel<T> p, Stage<T> st,
-                                                          double dt, const T *__restrict__ tab,
-                                                          const T *__restrict__ phi,
-                                                          const T *__restrict__ grad,
-                                                          T *__restrict__ phi_o,
-                                                          T *__restrict__ grad_o)
+__global__ __launch_bounds__(kBlock)
+    __attribute__((amdgpu_waves_per_eu(
+        kWaves3d<T, GALS_VEL_VECPOT_SIN, MIX, PSI>))) void k_step3d_vecpot(
+        Geom g, Vel<T> p, Stage<T> st, double dt, const T *__restrict__ tab,
+        const T *__restrict__ phi, const T *__restrict__ grad, T *__restrict__ phi_o,
+        T *__restrict__ grad_o)
 {
     constexpr bool LDS = sizeof(T) == 4;
     __shared__ T tab_s[LDS ? 24 : 1][kBlock];
@@ -606,8 +605,10 @@ __global__ __launch_bounds__(kBlock) void k_prepare(Geom g, Vel<double> p, unsig
             int r = id, a = 0;
             while (a < 3 && r >= g.n[a]) r -= g.n[a++];
             if (a >= 3) return;
+            // the vector potential's angles, twice the trig fields' (trace_trig)
+            const double turns = p.kind == GALS_VEL_VECPOT_SIN ? 1.0 : 2.0;
             double s, c;
-            sincospi(node_coord(g.lo[a], r, g.h[a]), &s, &c);
+            sincospi(turns * node_coord(g.lo[a], r, g.h[a]), &s, &c);
             tab0[2 * id] = T(s);
             tab0[2 * id + 1] = T(c);
         }

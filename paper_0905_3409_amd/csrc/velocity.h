@@ -82,34 +82,32 @@ __device__ __forceinline__ void shifted_sincos_long(T s1, T c1, T d, T &s, T &c)
     c = c1 * cd - s1 * sd;
 }
 
-// The FP64 series one term longer (to a^11 and a^12): the dropped terms stay
-// below 7e-19 up to |pi d| = 0.2, for fields run at a few cells per step on
-// coarse grids. FP32 takes shifted_sincos_long.
-template <typename T>
-constexpr double kShiftMaxWide = sizeof(T) == 8 ? 0.2 : kShiftMaxLong<T>;
-template <typename T>
-__device__ __forceinline__ void shifted_sincos_wide(T s1, T c1, T d, T &s, T &c)
+// sin and cos of 2 pi (x + d) from s = sin(2 pi x), c = cos(2 pi x), FP64, with the
+// series to a^13 and a^14: the dropped terms stay below 1e-18 up to |a| = 2 pi |d|
+// = 0.4. The shift enters as a correction of s and c (cm = cos a - 1), so that the
+// large terms are rounded once.
+constexpr double kShift2Max = 0.4;
+__device__ __forceinline__ void shifted_sincos2(double s0, double c0, double d, double &s,
+                                                double &c)
 {
-    if constexpr (sizeof(T) == 4) {
-        shifted_sincos_long(s1, c1, d, s, c);
-    } else {
-        const T a = T(kPi) * d, a2 = a * a;
-        const T sd =
-            a * (T(1) -
-                 a2 * (T(1.0 / 6) -
-                       a2 * (T(1.0 / 120) -
-                             a2 * (T(1.0 / 5040) -
-                                   a2 * (T(1.0 / 362880) - a2 * T(1.0 / 39916800))))));
-        const T cd =
-            T(1) -
-            a2 * (T(0.5) -
-                  a2 * (T(1.0 / 24) -
-                        a2 * (T(1.0 / 720) -
-                              a2 * (T(1.0 / 40320) -
-                                    a2 * (T(1.0 / 3628800) - a2 * T(1.0 / 479001600))))));
-        s = s1 * cd + c1 * sd;
-        c = c1 * cd - s1 * sd;
-    }
+    const double a = (2.0 * kPi) * d, a2 = a * a;
+    const double sd =
+        a * (1.0 -
+             a2 * (1.0 / 6 -
+                   a2 * (1.0 / 120 -
+                         a2 * (1.0 / 5040 -
+                               a2 * (1.0 / 362880 -
+                                     a2 * (1.0 / 39916800 - a2 * (1.0 / 6227020800.0)))))));
+    const double cm =
+        -a2 * (0.5 -
+               a2 * (1.0 / 24 -
+                     a2 * (1.0 / 720 -
+                           a2 * (1.0 / 40320 -
+                                 a2 * (1.0 / 3628800 -
+                                       a2 * (1.0 / 479001600 -
+                                             a2 * (1.0 / 87178291200.0)))))));
+    s = s0 + (c0 * sd + s0 * cm);
+    c = c0 + (c0 * cm - s0 * sd);
 }
 
 template <typename T>
@@ -251,16 +249,14 @@ __device__ __forceinline__ void vel_stream(const Params &p, const double *x, T c
     stream_modes(p, sx, cx, sy, cy, c, v, J);
 }
 
-// s = sin^2(pi x) sin^2(pi y) / pi, from sin and cos of pi x and pi y.
+// s = sin^2(pi x) sin^2(pi y) / pi, from q = sin^2(pi .), s2 = sin(2 pi .) and
+// c2 = cos(2 pi .).
 template <typename T>
-__device__ __forceinline__ void vortex_from(const T *s1, const T *c1, T c, T *v, T *J)
+__device__ __forceinline__ void vortex_from(const T *q, const T *s2, const T *c2, T c, T *v, T *J)
 {
-    const T qx = s1[0] * s1[0], qy = s1[1] * s1[1];                          // sin^2
-    const T s2x = T(2) * s1[0] * c1[0], s2y = T(2) * s1[1] * c1[1];          // sin(2 pi .)
-    const T c2x = T(1) - T(2) * qx, c2y = T(1) - T(2) * qy;                  // cos(2 pi .)
     const T pi = T(kPi);
-    from_stream(s2x * qy, qx * s2y, T(2) * pi * c2x * qy, pi * s2x * s2y, T(2) * pi * qx * c2y,
-                c, v, J);
+    from_stream(s2[0] * q[1], q[0] * s2[1], T(2) * pi * c2[0] * q[1], pi * s2[0] * s2[1],
+                T(2) * pi * q[0] * c2[1], c, v, J);
 }
 
 // v = exp(e.x) e, e = (sqrt 2, sqrt pi) / sqrt(2 + pi).
@@ -382,31 +378,25 @@ __device__ __forceinline__ void vel_vecpot(const Vel<T> &p, const double *x, T c
 
 // Divergence-free reading of the 3D deformation field of sec. 6.2:
 // u = 2 sin^2(pi x) sin(2 pi y) sin(2 pi z), v = -sin(2 pi x) sin^2(pi y) sin(2 pi z),
-// w = -sin(2 pi x) sin(2 pi y) sin^2(pi z), from sin and cos of pi x, pi y, pi z.
+// w = -sin(2 pi x) sin(2 pi y) sin^2(pi z), from q = sin^2(pi .), s2 = sin(2 pi .)
+// and e2 = 2 pi cos(2 pi .).
 template <typename T>
-__device__ __forceinline__ void leveque_from(const T *s1, const T *c1, T c, T *v, T *J)
+__device__ __forceinline__ void leveque_from(const T *q, const T *s2, const T *e2, T c, T *v, T *J)
 {
-    const T tpi = T(2 * kPi);
-    T q[3], s2[3], c2[3];  // sin^2, sin(2 pi .), 2 pi cos(2 pi .)
-    for (int i = 0; i < 3; i++) {
-        q[i] = s1[i] * s1[i];
-        s2[i] = T(2) * s1[i] * c1[i];
-        c2[i] = tpi - (T(2) * tpi) * q[i];
-    }
     const T u = T(2) * c * q[0], w = -c * s2[0];
     const T uz = u * s2[2], uy = u * s2[1], wy = w * q[1], wz = w * q[2];
-    const T d = -c * c2[0], p = (T(kPi) * w) * (s2[1] * s2[2]);
+    const T d = -c * e2[0], p = (T(kPi) * w) * (s2[1] * s2[2]);
     v[0] = uz * s2[1];
     v[1] = wy * s2[2];
     v[2] = wz * s2[1];
     J[0] = T(-2) * p;         // du/dx
-    J[1] = uz * c2[1];        // du/dy
-    J[2] = uy * c2[2];        // du/dz
+    J[1] = uz * e2[1];        // du/dy
+    J[2] = uy * e2[2];        // du/dz
     J[3] = d * q[1] * s2[2];  // dv/dx
     J[4] = p;                 // dv/dy
-    J[5] = wy * c2[2];        // dv/dz
+    J[5] = wy * e2[2];        // dv/dz
     J[6] = d * q[2] * s2[1];  // dw/dx
-    J[7] = wz * c2[1];        // dw/dy
+    J[7] = wz * e2[1];        // dw/dy
     J[8] = p;                 // dw/dz
 }
 
@@ -414,11 +404,38 @@ __device__ __forceinline__ void leveque_from(const T *s1, const T *c1, T c, T *v
 template <int KIND>
 constexpr bool kTrigField = KIND == GALS_VEL_VORTEX || KIND == GALS_VEL_LEVEQUE3D;
 
-template <typename T, int KIND>
-__device__ __forceinline__ void trig_field(const T *s1, const T *c1, T c, T *v, T *J)
+// From sin and cos of pi times the coordinates.
+template <typename T, int KIND, int D>
+__device__ __forceinline__ void trig_field(const T (&s1)[D], const T (&c1)[D], T c, T *v, T *J)
 {
-    if constexpr (KIND == GALS_VEL_VORTEX) vortex_from(s1, c1, c, v, J);
-    else leveque_from(s1, c1, c, v, J);
+    T q[D], s2[D], c2[D];
+#pragma unroll
+    for (int a = 0; a < D; a++) {
+        q[a] = s1[a] * s1[a];
+        s2[a] = T(2) * s1[a] * c1[a];
+        if constexpr (KIND == GALS_VEL_VORTEX) c2[a] = T(1) - T(2) * q[a];
+        else c2[a] = T(2 * kPi) - T(4 * kPi) * q[a];
+    }
+    if constexpr (KIND == GALS_VEL_VORTEX) vortex_from(q, s2, c2, c, v, J);
+    else leveque_from(q, s2, c2, c, v, J);
+}
+
+// From sin and cos of 2 pi times the coordinates: half the error in q where sin^2
+// is near 1, against the square of a rounded sine.
+template <typename T, int KIND, int D>
+__device__ __forceinline__ void trig_field2(const T (&s2)[D], const T (&c2)[D], T c, T *v, T *J)
+{
+    T q[D];
+#pragma unroll
+    for (int a = 0; a < D; a++) q[a] = T(0.5) - T(0.5) * c2[a];
+    if constexpr (KIND == GALS_VEL_VORTEX) {
+        vortex_from(q, s2, c2, c, v, J);
+    } else {
+        T e2[D];
+#pragma unroll
+        for (int a = 0; a < D; a++) e2[a] = T(2 * kPi) * c2[a];
+        leveque_from(q, s2, e2, c, v, J);
+    }
 }
 
 // Dispatch on the compile-time field kind (D = space dimension).
@@ -437,7 +454,7 @@ __device__ __forceinline__ void velocity(const Vel<T> &p, const double *x, T c, 
         T s1[D], c1[D];
 #pragma unroll
         for (int a = 0; a < D; a++) sincospi_t(T(x[a]), &s1[a], &c1[a]);
-        trig_field<T, KIND>(s1, c1, c, v, J);
+        trig_field<T, KIND, D>(s1, c1, c, v, J);
     }
 }
 
