@@ -32,7 +32,9 @@
  *   stream). Calls marked "async" only enqueue work on it.
  * Ownership: the caller allocates and owns every device buffer (state,
  *   workspace, points, outputs); the library owns only its context and never
- *   frees caller memory.
+ *   frees caller memory. Besides its contexts it holds, per process, one page
+ *   of pinned host memory from the first reduction on (gals_max_speed,
+ *   gals_norms, gals_shape_loss) and the scratch of gals_advance_noalloc.
  * Errors: every entry point returns GALS_OK (0) or a negative code and never
  *   throws; gals_last_error() returns a thread-local message describing the
  *   last failure. Asynchronous kernel faults surface as GALS_EHIP from a

@@ -306,31 +306,34 @@ int check_advance_args(const gals_ctx *ctx, const void *phi, const void *grad, d
 
 // ---------------------------------------------------------------------------
 // Results of the reductions that synchronise: one page of pinned host memory for
-// the process, allocated with the first device context and held until the process
-// ends, in slots of eight doubles. The folding kernel writes a slot directly and
-// the call reads it after its stream is done, without a copy from the device
-// (norms and largest speed on 2049^2 FP32 nodes: 91 us with the copies, 72 without). A
-// call holds a slot only while it waits, so streams and threads each have their
-// own; with no page or no free slot it goes through the workspace and a copy.
+// the process, allocated by the first of them and held until the process ends, in
+// slots of eight doubles. The folding kernel writes a slot directly and the call
+// reads it after its stream is done, without a copy from the device (norms and
+// largest speed on 2049^2 FP32 nodes: 91 us with the copies, 72 without). A call
+// holds a slot only while it waits, so streams and threads each have their own;
+// with no page or no free slot it goes through the workspace and a copy, and a
+// page that could not be had is asked for again by the next call.
 // ---------------------------------------------------------------------------
 constexpr int kResultSlots = 64;
 std::mutex g_result_mutex;
 double *g_result_page;     // kResultSlots x kRedSlots doubles
-bool g_result_tried;
 uint64_t g_result_used;    // one bit per slot
 
-// Allocate the page once; the context's device must be current.
-void result_page_init()
+// The page, or null if it cannot be had now. The context's device must be
+// current, and g_result_mutex held. Another thread may be capturing a stream:
+// the allocation is no part of its capture and must not end it.
+double *result_page()
 {
-    std::lock_guard<std::mutex> lock(g_result_mutex);
-    if (g_result_tried) return;
-    g_result_tried = true;
+    if (g_result_page) return g_result_page;
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    const bool relaxed = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
     void *p = nullptr;
     if (hipHostMalloc(&p, sizeof(double) * kResultSlots * kRedSlots, hipHostMallocPortable) ==
         hipSuccess)
         g_result_page = static_cast<double *>(p);
-    else
-        (void)hipGetLastError();
+    if (relaxed) (void)hipThreadExchangeStreamCaptureMode(&mode);
+    (void)hipGetLastError();
+    return g_result_page;
 }
 
 struct ResultSlot {
@@ -338,7 +341,7 @@ struct ResultSlot {
     ResultSlot()
     {
         std::lock_guard<std::mutex> lock(g_result_mutex);
-        if (!g_result_page || g_result_used == ~uint64_t(0)) return;
+        if (!result_page() || g_result_used == ~uint64_t(0)) return;
         slot = __builtin_ctzll(~g_result_used);
         g_result_used |= uint64_t(1) << slot;
     }
@@ -436,10 +439,6 @@ int gals_create(gals_ctx **out, int dim, const int64_t *ncell, const double *lo,
         if (e != hipSuccess) return hip_fail(e, "gals_create: hipGetDeviceCount");
         if (device < 0 || device >= count)
             return fail(GALS_EINVAL, "gals_create: device %d not in [0, %d)", device, count);
-    }
-    if (device >= 0) {
-        DeviceGuard dg(device);
-        if (dg.err == hipSuccess) result_page_init();
     }
     gals_ctx *c = new (std::nothrow) gals_ctx;
     if (!c) return fail(GALS_ENOMEM, "gals_create: out of host memory");
