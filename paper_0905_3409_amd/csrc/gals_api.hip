@@ -312,7 +312,8 @@ int check_advance_args(const gals_ctx *ctx, const void *phi, const void *grad, d
 // largest speed on 2049^2 FP32 nodes: 91 us with the copies, 72 without). A call
 // holds a slot only while it waits, so streams and threads each have their own;
 // with no page or no free slot it goes through the workspace and a copy, and a
-// page that could not be had is asked for again by the next call.
+// page that could not be had is asked for again by the next call. A call whose
+// wait fails never gives its slot back: its kernel may still write there.
 // ---------------------------------------------------------------------------
 constexpr int kResultSlots = 64;
 std::mutex g_result_mutex;
@@ -338,6 +339,7 @@ double *result_page()
 
 struct ResultSlot {
     int slot = -1;
+    bool written = false;  // a kernel that writes the slot may be under way
     ResultSlot()
     {
         std::lock_guard<std::mutex> lock(g_result_mutex);
@@ -347,7 +349,7 @@ struct ResultSlot {
     }
     ~ResultSlot()
     {
-        if (slot < 0) return;
+        if (slot < 0 || written) return;
         std::lock_guard<std::mutex> lock(g_result_mutex);
         g_result_used &= ~(uint64_t(1) << slot);
     }
@@ -648,14 +650,16 @@ int gals_eval_points(gals_ctx *ctx, const void *phi, const void *grad, const dou
 
 // Wait for a reduction's result, which its fold wrote to `res` (the slot's
 // memory, or device memory if there is none), and hand it over.
-static int finish_reduction(const ResultSlot &slot, const double *res, double *host_out, int n,
+static int finish_reduction(ResultSlot &slot, const double *res, double *host_out, int n,
                             hipStream_t s, const char *what)
 {
     hipError_t e = hipSuccess;
+    slot.written = true;
     if (!slot.get())
         e = hipMemcpyAsync(host_out, res, sizeof(double) * n, hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) return hip_fail(e, what);
+    slot.written = false;
     if (slot.get())
         for (int k = 0; k < n; k++) host_out[k] = slot.get()[k];
     return GALS_OK;
@@ -675,7 +679,7 @@ int gals_max_speed(gals_ctx *ctx, double t, double *out, void *workspace, size_t
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "gals_max_speed: pending HIP error");
     double *part = (double *)((char *)workspace + partial_offset(ctx));
-    const ResultSlot slot;
+    ResultSlot slot;
     double *res = slot.get() ? slot.get() : part + size_t(kRedBlocks) * kRedSlots;
     hipStream_t s = (hipStream_t)stream;
     e = launch_max_speed(ctx, time_factor(ctx->period, t), part, res, s);
@@ -699,7 +703,7 @@ int gals_norms(gals_ctx *ctx, const void *phi, const void *grad, const void *phi
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "gals_norms: pending HIP error");
     double *part = (double *)((char *)workspace + partial_offset(ctx));
-    const ResultSlot slot;
+    ResultSlot slot;
     double *res = slot.get() ? slot.get() : part + size_t(kRedBlocks) * kRedSlots;
     hipStream_t s = (hipStream_t)stream;
     e = launch_norms(ctx, phi, grad, phi_ref, grad_ref, eps, band, part, res, s);
@@ -973,7 +977,7 @@ int gals_shape_loss(gals_ctx *ctx, const void *phi, const void *phi_ref, double 
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "gals_shape_loss: pending HIP error");
     double *part = (double *)((char *)workspace + partial_offset(ctx));
-    const ResultSlot slot;
+    ResultSlot slot;
     double *res = slot.get() ? slot.get() : part + size_t(kRedBlocks) * kRedSlots;
     hipStream_t s = (hipStream_t)stream;
     e = launch_heaviside_loss(ctx, phi, phi_ref, eps, lam, part, res, s);

@@ -79,3 +79,24 @@ knob("malloc_fails").value = 0
 rc, v, where = speed(9.0)
 assert (rc, v) == (pkg.OK, 9.0) and not in_ws(where) and copies.value == 3
 """)
+
+
+def test_a_slot_whose_wait_failed_is_not_used_again(fake):
+    _run(fake, """
+knob("sync_fails").value = 1
+lost = set()
+for k in range(70):
+    rc, v, where = speed(3.5)
+    assert rc == pkg.EHIP and where not in lost
+    if in_ws(where):
+        break
+    assert v == -1.0
+    lost.add(where)
+assert len(lost) == 64  # then every slot is lost, and the workspace serves
+knob("sync_fails").value = 0
+for p in lost:  # the kernels of the failed calls write at last
+    ctypes.memmove(p, np.full(8, -7.0).ctypes.data, 64)
+for k in range(3):
+    rc, v, where = speed(4.0 + k)
+    assert (rc, v) == (pkg.OK, 4.0 + k) and in_ws(where)
+""")
