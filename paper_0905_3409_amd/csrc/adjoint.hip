@@ -231,6 +231,9 @@ __device__ __forceinline__ bool chunk_tile(const Geom &g, unsigned &tx, unsigned
 // and 17 with 15 % of them live (a band of 6 cells to each side, 20 steps). The
 // look costs a lambda without zeros 1 % (10 steps and the recomputed states
 // 620 -> 627 us).
+// Where every wave has work, data that are not finite make the parameter derivative
+// NaN from every foot that reads them, as 0 times them, whatever lambda. `dead`
+// says how a wave without lambda keeps that (adjoint_dead_waves).
 // Four waves per SIMD in FP32 (at most 128 VGPRs): an earlier form took 134
 // and three waves by default, 80 us per step on the 1024^2 gradient workload
 // against 68 at four. The FP64 kernel would spill heavily and keeps the
@@ -240,7 +243,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
     sizeof(T) == 4 ? 4 : 1))) void k_adjoint2d_stream(
     Geom g, Vel<T> p, Stage<T> st, double dt, const T *__restrict__ coltab,
     const T *__restrict__ rowtab, const T *__restrict__ phi, const T *__restrict__ grad,
-    double *__restrict__ lam_in, double *__restrict__ lam_out, double *__restrict__ partials)
+    double *__restrict__ lam_in, double *__restrict__ lam_out, double *__restrict__ partials,
+    DeadWaves dead)
 {
     unsigned tx, ty;
     const bool in_grid = chunk_tile(g, tx, ty);
@@ -251,22 +255,20 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
     int cell0 = 0, cell1 = 0;
     const bool in_row = in_grid && i < g.n[0] && j < g.n[1];
     const int64_t o = int64_t(j) * g.pitch + i;
-    double lf = 0.0, lx = 0.0, ly = 0.0;
+    double lf = 0.0, lx = 0.0, ly = 0.0, poison = 0.0;
     if (in_row) {
         lf = lam_in[o];
         lx = lam_in[o + g.plane];
         ly = lam_in[o + 2 * g.plane];
+        if (dead == DeadWaves::kSkipOwnData)
+            poison = double(T(0) * phi[o] + T(0) * grad[o] + T(0) * (grad + g.plane)[o]);
     }
     // A wave whose lambda is all +0 has nothing to add: its shares and its
     // parameter derivative are products with lambda. It skips the trace, and
-    // a block of such waves the rest; data that are not finite still reach the
-    // derivative as 0 times them.
+    // a block of such waves the rest.
     const uint64_t bits = __builtin_bit_cast(uint64_t, lf) | __builtin_bit_cast(uint64_t, lx) |
                           __builtin_bit_cast(uint64_t, ly);
-    const bool live = __builtin_amdgcn_ballot_w64(bits != 0) != 0;
-    double poison = 0.0;
-    if (!live && in_row)
-        poison = double(T(0) * phi[o] + T(0) * grad[o] + T(0) * (grad + g.plane)[o]);
+    const bool live = dead == DeadWaves::kWork || __builtin_amdgcn_ballot_w64(bits != 0) != 0;
 #pragma unroll
     for (int q = 0; q < 16; q++) gacc[q] = poison;
     const bool valid = in_row && live;
@@ -543,6 +545,27 @@ __global__ __launch_bounds__(kBlock) void k_heaviside_loss(Geom g, const T *__re
     block_reduce<1>(acc, 0u, partials + int64_t(blockIdx.x) * kRedSlots);
 }
 
+// What a wave without lambda has to do so that dF/dS is NaN exactly when the foot of
+// any node reads data that are not finite, in step n of a sweep of `steps` steps
+// (n = 0, steps = 1 for a step by itself):
+// - Feet less than a cell from their nodes (by the field's bound): a node is a
+//   vertex of its own foot's cell, so the values at the wave's own nodes tell.
+// - A later state of a sweep: a value that is not finite there came from a foot of
+//   the step before, which made dF/dS NaN; so again the own values tell, also for
+//   what the step before read.
+// - The first state of a sweep of several steps: what its feet read shows in the
+//   second state, and what none reads is not to be looked at.
+// - A step by itself with longer feet: only the feet tell, so every wave works.
+// Values that are finite but overflow in the bicubic's second derivatives reach dF/dS
+// through waves with lambda alone.
+DeadWaves adjoint_dead_waves(const gals_ctx *ctx, double dt, int64_t n, int64_t steps)
+{
+    double b[2];
+    stream_reach(ctx, dt, 1.0, 1.0, 1.0, b);
+    if (n > 0 || (b[0] < 1.0 && b[1] < 1.0)) return DeadWaves::kSkipOwnData;
+    return steps > 1 ? DeadWaves::kSkip : DeadWaves::kWork;
+}
+
 unsigned adjoint_blocks(const gals_ctx *ctx)
 {
     return (ctx->g.tiles + 7u) / 8u * 8u;
@@ -550,21 +573,21 @@ unsigned adjoint_blocks(const gals_ctx *ctx)
 
 template <typename T, int MIX>
 static void launch_adj(const gals_ctx *ctx, const Vel<T> &p, const void *phi, const void *grad,
-                       double *lam_in, double *lam_out, bool clear, double *partials, double dt,
-                       double c1, double c2, double c3, const void *coltab, const void *rowtab,
-                       hipStream_t s)
+                       double *lam_in, double *lam_out, bool clear, double *partials,
+                       DeadWaves dead, double dt, double c1, double c2, double c3,
+                       const void *coltab, const void *rowtab, hipStream_t s)
 {
     const Stage<T> st = make_stage<T>(dt, c1, c2, c3);
     if (clear)
         hipLaunchKernelGGL((k_adjoint2d_stream<T, MIX, sizeof(T) == 4, true>),
                            dim3(adjoint_blocks(ctx)), dim3(kBlock), 0, s, ctx->g, p, st, dt,
                            (const T *)coltab, (const T *)rowtab, (const T *)phi, (const T *)grad,
-                           lam_in, lam_out, partials);
+                           lam_in, lam_out, partials, dead);
     else
         hipLaunchKernelGGL((k_adjoint2d_stream<T, MIX, sizeof(T) == 4, false>),
                            dim3(adjoint_blocks(ctx)), dim3(kBlock), 0, s, ctx->g, p, st, dt,
                            (const T *)coltab, (const T *)rowtab, (const T *)phi, (const T *)grad,
-                           lam_in, lam_out, partials);
+                           lam_in, lam_out, partials, dead);
 }
 
 hipError_t launch_zero(double *p, int64_t n, hipStream_t s)
@@ -578,12 +601,12 @@ hipError_t launch_zero(double *p, int64_t n, hipStream_t s)
 
 hipError_t launch_adjoint_step(const gals_ctx *ctx, const void *phi, const void *grad,
                                double *lam_in, double *lam_out, bool clear, double *partials,
-                               double dt, double c1, double c2, double c3, const void *coltab,
-                               const void *rowtab, hipStream_t s)
+                               DeadWaves dead, double dt, double c1, double c2, double c3,
+                               const void *coltab, const void *rowtab, hipStream_t s)
 {
-#define GALS_ADJ(T, V, M)                                                                   \
-    launch_adj<T, M>(ctx, ctx->V, phi, grad, lam_in, lam_out, clear, partials, dt, c1, c2, c3, \
-                     coltab, rowtab, s)
+#define GALS_ADJ(T, V, M)                                                                      \
+    launch_adj<T, M>(ctx, ctx->V, phi, grad, lam_in, lam_out, clear, partials, dead, dt, c1, c2, \
+                     c3, coltab, rowtab, s)
     if (ctx->prec == GALS_F32) {
         if (ctx->mixed == GALS_MIXED_ZERO) GALS_ADJ(float, vf, GALS_MIXED_ZERO);
         else if (ctx->mixed == GALS_MIXED_CELL) GALS_ADJ(float, vf, GALS_MIXED_CELL);

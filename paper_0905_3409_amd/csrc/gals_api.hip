@@ -901,7 +901,8 @@ int gals_adjoint(gals_ctx *ctx, const void *ckpt, size_t ckpt_bytes, double t0, 
         for (int64_t q = len - 1; q >= 0 && e == hipSuccess; q--) {
             const double t = t0 + double(n0 + q) * dt;
             const char *u = at(q);
-            e = launch_adjoint_step(ctx, u, u + pb, lamA, lamB, true, part, dt,
+            e = launch_adjoint_step(ctx, u, u + pb, lamA, lamB, true, part,
+                                    adjoint_dead_waves(ctx, dt, n0 + q, steps), dt,
                                     time_factor(ctx->period, t + dt), time_factor(ctx->period, t),
                                     time_factor(ctx->period, t + 0.5 * dt), coltab, rowtab, s);
             double *tmp = lamA;
@@ -953,7 +954,8 @@ int gals_adjoint_step(gals_ctx *ctx, const void *phi, const void *grad, double t
     if (e == hipSuccess) e = launch_zero(part, int64_t(nblocks) * 16, s);
     if (e == hipSuccess) e = launch_zero(lam_out, 3 * ctx->g.plane, s);
     if (e == hipSuccess)
-        e = launch_adjoint_step(ctx, phi, grad, const_cast<double *>(lam_in), lam_out, false, part, dt,
+        e = launch_adjoint_step(ctx, phi, grad, const_cast<double *>(lam_in), lam_out, false, part,
+                                adjoint_dead_waves(ctx, dt, 0, 1), dt,
                                 time_factor(ctx->period, t + dt), time_factor(ctx->period, t),
                                 time_factor(ctx->period, t + 0.5 * dt), coltab, rowtab, s);
     if (e == hipSuccess) e = launch_fold_grad(part, nblocks, dS, s);

@@ -239,6 +239,9 @@ hipError_t launch_step(const gals_ctx *ctx, const void *phi, const void *grad, v
 // up to k <= kMultiSteps of them (time factors c[q]) and says how many in *took,
 // 0 if not even two fit (then nothing was launched).
 constexpr int kMultiSteps = 4;
+// Bound of a foot's displacement along each axis, in cells, for a sine stream
+// function and time factors up to c1, c2, c3 in size.
+void stream_reach(const gals_ctx *ctx, double dt, double c1, double c2, double c3, double reach[2]);
 int multi_steps(const gals_ctx *ctx, double dt);
 hipError_t launch_multi_step(const gals_ctx *ctx, int k, const double (*c)[3], const void *phi,
                              const void *grad, void *phi_o, void *grad_o, double dt,
@@ -267,11 +270,15 @@ hipError_t launch_face(const gals_ctx *ctx, const void *sphi, const void *sgrad,
 // Adjoint of the stream-function step and the shape loss (adjoint.hip).
 // adjoint_blocks: blocks of the adjoint launch (16 partials each).
 unsigned adjoint_blocks(const gals_ctx *ctx);
+// What an adjoint step's waves do whose lambda is zero: their work all the same, or
+// skip it, with or without a look at their own nodes' data.
+enum class DeadWaves { kWork, kSkip, kSkipOwnData };
+DeadWaves adjoint_dead_waves(const gals_ctx *ctx, double dt, int64_t n, int64_t steps);
 // lam_out must hold zeros; clear: zero lam_in as it is read.
 hipError_t launch_adjoint_step(const gals_ctx *ctx, const void *phi, const void *grad,
                                double *lam_in, double *lam_out, bool clear, double *partials,
-                               double dt, double c1, double c2, double c3, const void *coltab,
-                               const void *rowtab, hipStream_t s);
+                               DeadWaves dead, double dt, double c1, double c2, double c3,
+                               const void *coltab, const void *rowtab, hipStream_t s);
 hipError_t launch_zero(double *p, int64_t n, hipStream_t s);
 hipError_t launch_fold_grad(const double *partials, int nparts, double *out, hipStream_t s);
 hipError_t launch_heaviside_loss(const gals_ctx *ctx, const void *phi, const void *phi_ref,

@@ -255,6 +255,20 @@ static bool multi_plan(const Geom &g, const F &f, int k, int &cap, size_t &bytes
     return bytes <= kMultiLds;
 }
 
+void stream_reach(const gals_ctx *ctx, double dt, double c1, double c2, double c3, double reach[2])
+{
+    double sx = 0.0, sy = 0.0;  // bounds of |s_x| and |s_y|, everywhere
+    for (int m = 0; m < 4; m++)
+        for (int n = 0; n < 4; n++) {
+            sx += fabs(ctx->vd.S[m][n]) * (m + 1) * kPi;
+            sy += fabs(ctx->vd.S[m][n]) * (n + 1) * kPi;
+        }
+    // the stage weights' sum, and room for the rounding of a displacement
+    const double w = 1.001 * dt * (fabs(c1) / 6.0 + fabs(c2) / 6.0 + fabs(c3) * 2.0 / 3.0);
+    reach[0] = w * sy * ctx->g.inv_h[0];
+    reach[1] = w * sx * ctx->g.inv_h[1];
+}
+
 template <typename T>
 static void fill_steps(const gals_ctx *ctx, const Vel<T> &, int k, const double (*c)[3], double dt,
                        AffineSteps<T> &f)
@@ -267,22 +281,13 @@ template <typename T>
 static void fill_steps(const gals_ctx *ctx, const Vel<T> &p, int k, const double (*c)[3], double dt,
                        StreamSteps<T> &f)
 {
-    double sx = 0.0, sy = 0.0;  // bounds of |s_x| and |s_y|, everywhere
     for (int m = 0; m < 4; m++)
-        for (int n = 0; n < 4; n++) {
-            f.S[m][n] = p.S[m][n];
-            sx += fabs(ctx->vd.S[m][n]) * (m + 1) * kPi;
-            sy += fabs(ctx->vd.S[m][n]) * (n + 1) * kPi;
-        }
+        for (int n = 0; n < 4; n++) f.S[m][n] = p.S[m][n];
     f.kx = p.kx;
     f.ky = p.ky;
     for (int q = 0; q < k; q++) {
         f.st[q] = make_stage<T>(dt, c[q][0], c[q][1], c[q][2]);
-        // the stage weights' sum, and room for the rounding of a displacement
-        const double w =
-            1.001 * dt * (fabs(c[q][0]) / 6.0 + fabs(c[q][1]) / 6.0 + fabs(c[q][2]) * 2.0 / 3.0);
-        f.bound[q][0] = w * sy * ctx->g.inv_h[0];
-        f.bound[q][1] = w * sx * ctx->g.inv_h[1];
+        stream_reach(ctx, dt, c[q][0], c[q][1], c[q][2], f.bound[q]);
     }
 }
 
