@@ -59,7 +59,10 @@ struct Region {
 
 // The nodes that the stencils of feet in [ax, bx] x [ay, by] (cell units) read:
 // cells clamped into the grid, as the feet's are. kSlack covers the rounding
-// between this estimate and a node's own foot.
+// between this estimate and a node's own foot: an FP32 displacement of up to
+// kMaxCells32 cells is off by at most 4.9e-4 (fill_steps refuses longer axes, and
+// numbers for which a foot may be NaN).
+constexpr int kMaxCells32 = 8192;
 __host__ __device__ inline Region stencil_region(const Geom &g, double ax, double bx, double ay,
                                                  double by)
 {
@@ -91,7 +94,7 @@ struct AffineSteps {
         const AffineMap2<T> &q = m[s];
         const double ex = fabs(q.Mc[0]) * (w - 1) + fabs(q.Mc[1]) * (h - 1);
         const double ey = fabs(q.Mc[2]) * (w - 1) + fabs(q.Mc[3]) * (h - 1);
-        // a NaN or a far-flung map gives the largest value: no plan fits it
+        // a far-flung map needs the whole grid (multi_plan clips to it)
         w = ex < 1e6 ? int(ex + 0.01) + 5 : 1 << 20;
         h = ey < 1e6 ? int(ey + 0.01) + 3 : 1 << 20;
     }
@@ -269,26 +272,42 @@ void stream_reach(const gals_ctx *ctx, double dt, double c1, double c2, double c
     reach[1] = w * sx * ctx->g.inv_h[1];
 }
 
+// Fill f; false if its regions would not hold: numbers so large that a foot may be
+// NaN (its cell is then not where the region is), or FP32 displacements that round
+// by more than the regions' slack.
 template <typename T>
-static void fill_steps(const gals_ctx *ctx, const Vel<T> &, int k, const double (*c)[3], double dt,
+static bool fill_steps(const gals_ctx *ctx, const Vel<T> &, int k, const double (*c)[3], double dt,
                        AffineSteps<T> &f)
 {
-    for (int q = 0; q < k; q++)
+    bool sound = sizeof(T) == 8 || (ctx->g.nc[0] <= kMaxCells32 && ctx->g.nc[1] <= kMaxCells32);
+    for (int q = 0; q < k; q++) {
         f.m[q] = affine_map2(make_affine_map<T>(ctx, dt, c[q][0], c[q][1], c[q][2]));
+        for (int a = 0; a < 2; a++)
+            for (double v : {f.m[q].kc[a], f.m[q].Mc[2 * a], f.m[q].Mc[2 * a + 1]})
+                sound = sound && fabs(v) <= __DBL_MAX__;
+    }
+    return sound;
 }
 
 template <typename T>
-static void fill_steps(const gals_ctx *ctx, const Vel<T> &p, int k, const double (*c)[3], double dt,
+static bool fill_steps(const gals_ctx *ctx, const Vel<T> &p, int k, const double (*c)[3], double dt,
                        StreamSteps<T> &f)
 {
+    // the field's derivatives, up to the fourth, and dt stay numbers in T
+    constexpr double kLargest = sizeof(T) == 4 ? 1e30 : 1e290;
+    bool sound = dt <= kLargest;
     for (int m = 0; m < 4; m++)
-        for (int n = 0; n < 4; n++) f.S[m][n] = p.S[m][n];
+        for (int n = 0; n < 4; n++) {
+            f.S[m][n] = p.S[m][n];
+            sound = sound && fabs(ctx->vd.S[m][n]) <= kLargest;
+        }
     f.kx = p.kx;
     f.ky = p.ky;
     for (int q = 0; q < k; q++) {
         f.st[q] = make_stage<T>(dt, c[q][0], c[q][1], c[q][2]);
         stream_reach(ctx, dt, c[q][0], c[q][1], c[q][2], f.bound[q]);
     }
+    return sound;
 }
 
 // Steps per launch for time factors of 1 (the largest displacements).
@@ -298,7 +317,7 @@ static int choose_steps(const gals_ctx *ctx, const Vel<T> &p, double dt)
     F f;
     double c[kMultiMax][3];
     for (int q = 0; q < kMultiMax; q++) c[q][0] = c[q][1] = c[q][2] = 1.0;
-    fill_steps(ctx, p, kMultiMax, c, dt, f);
+    if (!fill_steps(ctx, p, kMultiMax, c, dt, f)) return 1;
     for (int k = kMultiMax; k > 1; k--) {
         int cap, updates, passes;
         size_t bytes;
@@ -336,7 +355,6 @@ static hipError_t launch_multi(const gals_ctx *ctx, const F &f, int k, const voi
     int cap = 0, updates, passes;
     size_t bytes = 0;
     while (k > 1 && !multi_plan<T>(ctx->g, f, k, cap, bytes, updates, passes)) k--;
-    *took = 0;
     if (k < 2) return hipSuccess;
     *took = k;
     return with_modes(ctx->mixed, ctx->psi, [&](auto mix, auto psi) -> hipError_t {
@@ -354,13 +372,14 @@ static hipError_t multi_typed(const gals_ctx *ctx, const Vel<T> &p, int k, const
                               double dt, const void *coltab, const void *rowtab, hipStream_t s,
                               int *took)
 {
+    *took = 0;
     if (ctx->vel_kind == GALS_VEL_AFFINE) {
         AffineSteps<T> f;
-        fill_steps(ctx, p, k, c, dt, f);
+        if (!fill_steps(ctx, p, k, c, dt, f)) return hipSuccess;
         return launch_multi<T>(ctx, f, k, phi, grad, phi_o, grad_o, dt, s, took);
     }
     StreamSteps<T> f;
-    fill_steps(ctx, p, k, c, dt, f);
+    if (!fill_steps(ctx, p, k, c, dt, f)) return hipSuccess;
     f.coltab = (const T *)coltab;
     f.rowtab = (const T *)rowtab;
     return launch_multi<T>(ctx, f, k, phi, grad, phi_o, grad_o, dt, s, took);
