@@ -90,3 +90,17 @@ def test_numbers_out_of_range(probe, f32):
                     S[5], S[2] = s, s
                     bad, k = probe(f32, 0, ncell, S, dt)
                     assert bad == 0, (ncell, dt, s, k)
+
+
+SHORT = dict(ncell=(200, 200), par=[0, 0, 0.5, 0.5, 7, 0, 0, 7], dt=0.1)
+
+
+@pytest.mark.parametrize("f32", [False, True])
+def test_a_launch_takes_fewer_steps_than_planned(probe, f32):
+    """The case of test_gpu_multi_short: a contracting field that expands when its
+    time factor changes sign."""
+    assert probe(f32, 1, SHORT["ncell"], SHORT["par"], SHORT["dt"])[1] == 4
+    taken = {probe(f32, 1, SHORT["ncell"], SHORT["par"], SHORT["dt"], 1.0, 0.55 + 0.1 * n)[1]
+             for n in range(8)}
+    print("steps taken", taken)
+    assert min(taken) < 4
