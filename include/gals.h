@@ -275,13 +275,13 @@ int gals_advance_save(gals_ctx *ctx, void *phi, void *grad, double t0, double dt
                       int64_t every, void *ckpt, size_t ckpt_bytes, void *workspace,
                       size_t workspace_bytes, void *stream);
 /* Workspace bytes of gals_adjoint with checkpoints every `every` steps (and,
- * with every = 1, of gals_adjoint_step): the advance's workspace, `every`
+ * with every = 1, of gals_adjoint_step): the advance's workspace, every - 1
  * recomputed states, one adjoint state and the dF/dS partials. */
 int gals_adjoint_workspace_bytes(const gals_ctx *ctx, int64_t every, size_t *bytes);
 /* Reverse sweep of the advance stored by gals_advance_save (same t0, dt,
  * steps, every, velocity): lam holds dF/du at the final state on entry and
  * dF/du at the initial state on return; dS receives dF/dS (overwritten).
- * Recomputes each segment of `every` states from its checkpoint. Async. */
+ * Recomputes the states of each segment after its checkpoint. Async. */
 int gals_adjoint(gals_ctx *ctx, const void *ckpt, size_t ckpt_bytes, double t0, double dt,
                  int64_t steps, int64_t every, double *lam, double *dS, void *workspace,
                  size_t workspace_bytes, void *stream);

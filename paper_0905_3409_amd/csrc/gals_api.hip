@@ -721,8 +721,9 @@ int gals_norms(gals_ctx *ctx, const void *phi, const void *grad, const void *phi
 
 /* ---------------------------------------------------------------------------
  * Adjoint of the advance (2D sine stream-function fields).
- * Workspace: [forward workspace | `every` segment states | one adjoint state
- * (3 FP64 planes) | per-block partials of dF/dS (16 FP64 each)].
+ * Workspace: [forward workspace | the states of a segment after its first, which
+ * is the checkpoint: every - 1 | one adjoint state (3 FP64 planes) | per-block
+ * partials of dF/dS (16 FP64 each)].
  * ------------------------------------------------------------------------- */
 }  // extern "C"
 
@@ -734,7 +735,7 @@ size_t lam_bytes(const gals_ctx *c) { return 3 * size_t(c->g.plane) * sizeof(dou
 size_t adj_seg_offset(const gals_ctx *c) { return align256(workspace_bytes(c)); }
 size_t adj_lam_offset(const gals_ctx *c, int64_t every)
 {
-    return adj_seg_offset(c) + size_t(every) * seg_state_bytes(c);
+    return adj_seg_offset(c) + size_t(every - 1) * seg_state_bytes(c);
 }
 size_t adj_part_offset(const gals_ctx *c, int64_t every)
 {
@@ -887,12 +888,12 @@ int gals_adjoint(gals_ctx *ctx, const void *ckpt, size_t ckpt_bytes, double t0, 
         // recompute the states of this segment from its checkpoint, which is
         // the first of them
         const char *slot = (const char *)ckpt + size_t(k) * sb;
-        auto at = [&](int64_t q) -> const char * { return q ? seg + size_t(q) * sb : slot; };
+        auto at = [&](int64_t q) -> const char * { return q ? seg + size_t(q - 1) * sb : slot; };
         const void *coltab_c = coltab, *rowtab_c = rowtab;
         for (int64_t q = 1; q < len && e == hipSuccess; q++) {
             const double t = t0 + double(n0 + q - 1) * dt;
             const char *src = at(q - 1);
-            char *dst = seg + size_t(q) * sb;
+            char *dst = seg + size_t(q - 1) * sb;
             e = launch_step(ctx, src, src + pb, dst, dst + pb, dt,
                             time_factor(ctx->period, t + dt), time_factor(ctx->period, t),
                             time_factor(ctx->period, t + 0.5 * dt), coltab_c, rowtab_c, s);
