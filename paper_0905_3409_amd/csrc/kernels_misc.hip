@@ -244,8 +244,11 @@ __global__ __launch_bounds__(kBlock) void k_max_speed(Geom g, Vel<T> p, T c,
 // rows: a thread keeps its column's sines and cosines, the block the tile's row
 // sums P_m = sum_n S sin(n pi y), Q_m = sum_n S (n pi) cos(n pi y) in LDS, and a
 // node is eight multiply-adds, those of stream_modes in its order. 2049^2 FP32:
-// 26 us with both sines and the row sums at every node, 7 with this.
-constexpr int kSpeedRows = 32;
+// 26 us with both sines and the row sums at every node, 7 with this. On grids of a
+// few columns most of a tile's threads have none: from kSpeedColumns on (us per
+// call, node by node / in tiles, FP64: 3 x 2000001 70 / 146, 8 x 1000001 83 / 84, 32 x
+// 400001 113 / 47; FP32: 59 / 130, 68 / 75, 90 / 43).
+constexpr int kSpeedRows = 32, kSpeedColumns = 12;
 
 template <typename T>
 __global__ __launch_bounds__(kBlock) void k_max_speed_stream(Geom g, Vel<T> p, T c,
@@ -309,7 +312,10 @@ static hipError_t max_speed_typed(const gals_ctx *ctx, const Vel<T> &p, double c
         hipLaunchKernelGGL((k_max_speed<T, 2, GALS_VEL_AFFINE>), grid, block, 0, s, ctx->g, p, cc, partials);
         break;
     case 2 * 16 + GALS_VEL_STREAM_SIN:
-        hipLaunchKernelGGL((k_max_speed_stream<T>), grid, block, 0, s, ctx->g, p, cc, partials);
+        if (ctx->g.n[0] < kSpeedColumns)
+            hipLaunchKernelGGL((k_max_speed<T, 2, GALS_VEL_STREAM_SIN>), grid, block, 0, s, ctx->g, p, cc, partials);
+        else
+            hipLaunchKernelGGL((k_max_speed_stream<T>), grid, block, 0, s, ctx->g, p, cc, partials);
         break;
     case 2 * 16 + GALS_VEL_VORTEX:
         hipLaunchKernelGGL((k_max_speed<T, 2, GALS_VEL_VORTEX>), grid, block, 0, s, ctx->g, p, cc, partials);
