@@ -900,18 +900,19 @@ __device__ __forceinline__ void tricubic_central(const Geom &g, Rsrc rphi, Rsrc 
     G[0] = hx; G[1] = hy; G[2] = hz;
     if constexpr (SECOND) {
         // a point on a vertex takes its data as they are, also on one of the grid's
-        // last nodes, which are far vertices of their cells (on the first vertex
-        // the sums above are exact)
+        // last nodes, which are far vertices of their cells (on the first vertex the
+        // sums above are exact); data of the cell that are not finite show as they
+        // do at its other points, as 0 times them
         bool on = true;
 #pragma unroll
         for (int a = 0; a < 3; a++) on = on && (xi[a] == T(0) || xi[a] == T(1));
         if (__builtin_expect(on, 0)) {
             const unsigned o = o0 + (xi[0] == T(1) ? 1u : 0u) + (xi[1] == T(1) ? P : 0u) +
                                (xi[2] == T(1) ? S : 0u);
-            H = bload(rphi, o, T());
-            G[0] = bload(rgx, o, T());
-            G[1] = bload(rgy, o, T());
-            G[2] = bload(rgz, o, T());
+            H = bload(rphi, o, T()) + T(0) * H;
+            G[0] = bload(rgx, o, T()) + T(0) * G[0];
+            G[1] = bload(rgy, o, T()) + T(0) * G[1];
+            G[2] = bload(rgz, o, T()) + T(0) * G[2];
         }
     }
 }

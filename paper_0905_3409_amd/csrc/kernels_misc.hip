@@ -246,8 +246,8 @@ __global__ __launch_bounds__(kBlock) void k_max_speed(Geom g, Vel<T> p, T c,
 // node is eight multiply-adds, those of stream_modes in its order. 2049^2 FP32:
 // 26 us with both sines and the row sums at every node, 7 with this. On grids of a
 // few columns most of a tile's threads have none: from kSpeedColumns on (us per
-// call, node by node / in tiles, FP64: 3 x 2000001 70 / 146, 8 x 1000001 83 / 84, 32 x
-// 400001 113 / 47; FP32: 59 / 130, 68 / 75, 90 / 43).
+// call, node by node / in tiles, FP64: 3 x 2000001 52 / 146, 8 x 1000001 62 / 84, 32 x
+// 400001 104 / 47; FP32: 40 / 130, 45 / 75, 80 / 43).
 constexpr int kSpeedRows = 32, kSpeedColumns = 12;
 
 template <typename T>
