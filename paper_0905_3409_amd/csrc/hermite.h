@@ -685,15 +685,17 @@ __device__ __forceinline__ void hermite3d_full(const T d[8][8], const Basis<T> &
 // (error of the FP32 curvature on 257^3 nodes 1.5e-5 with neither, 8e-6 with the
 // first, 2.9e-6 with both).
 //
-// Bound: vector issue (FP64 and the vector potential), the L1's rate for 64
-// scattered loads a node where the trace is cheap. Measured against forming
-// the cross derivatives, us per step on one box: 257^3 FP32 vector potential
-// 610 -> 540, 101^3 FP64 deformation field 53 -> 43, 141 x 131 x 121 FP64
-// vector potential 250 -> 185, 385^3 FP32 rotation 980 -> 935; 10^6 points in
-// FP32 363 -> 334 (with their transposed copy). Loads grouped by x node instead of by row cost the rotation 15 %
-// and the points 75 % (a row's loads no longer meet in the L1); two or three
-// groups in flight measured no faster than one and took the FP64 kernels from
-// three waves per SIMD to two.
+// Bound: vector issue (FP64 and the vector potential), the L1's rate for a node's
+// scattered rows (20 loads in FP32, 32 in FP64) where the trace is cheap. Measured
+// against forming the cross derivatives, both with one load per value, us per step
+// on one box: 257^3 FP32 vector potential 610 -> 540, 101^3 FP64 deformation field
+// 53 -> 43, 141 x 131 x 121 FP64 vector potential 250 -> 185, 385^3 FP32 rotation
+// 980 -> 935; 10^6 points in FP32 363 -> 334 (with their transposed copy). A row's
+// nodes by wide loads: 101^3 FP64 deformation field 45 -> 42, FP64 rotation 92 ->
+// 62. Loads grouped by x node instead of by row cost the rotation 15 % and the
+// points 75 % (a row's loads no longer meet in the L1); two or three groups in
+// flight measured no faster than one and took the FP64 kernels from three waves per
+// SIMD to two.
 // ---------------------------------------------------------------------------
 template <typename T>
 struct StencilWeights {
@@ -868,7 +870,7 @@ __device__ __forceinline__ void tricubic_central(const Geom &g, Rsrc rphi, Rsrc 
         }
     };
     // A group's loads are issued before the previous group's sums, and the sums
-    // are pinned there: left to itself the compiler issues all 64 loads first
+    // are pinned there: left to itself the compiler issues every load first
     // and holds their values (the FP32 vector potential then spills).
     T u[2][8];
     load(0, u[0]);

@@ -11,6 +11,12 @@
 // or within the field's largest displacement of it, and the stencil of its
 // cell adds one column below and two above, no row below and one above.
 //
+// The recomputed nodes (up to 6.6 times the tile's) cost a chip with little else to do
+// nothing. With eight grids at work, each on a stream of its own, a launch of several
+// steps still gains or is even (us for 64 steps of all eight, one step a launch ->
+// this: FP64 rotation 101^2 1490 -> 517, 181^2 1346 -> 606, 257^2 1381 -> 1052; stream
+// function 101^2 FP64 1449 -> 1159, 181^2 FP32 1446 -> 830).
+//
 // The node arithmetic is the single step's (split_disp, split_cells,
 // affine_values; stream_trace, stream_values; the same LDS or global gather
 // values), so results agree bit for bit with steps launched one by one.
