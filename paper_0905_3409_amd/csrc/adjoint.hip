@@ -284,8 +284,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
         }
 
         T d[4][4];
-        gather2d<T, MIX>(g, plane_rsrc(phi, g.span), plane_rsrc(grad, g.span),
-                         plane_rsrc(grad + g.plane, g.span), f.cell[0], f.cell[1], d);
+        gather2d<T, MIX>(g, plane_rsrc(phi, g.plane), plane_rsrc(grad, g.plane),
+                         plane_rsrc(grad + g.plane, g.plane), f.cell[0], f.cell[1], d);
         Basis<T> bx, by;
         basis<T, true>(T(f.xi[0]), geo_h<T>(g, 0), geo_ih<T>(g, 0), bx);
         basis<T, true>(T(f.xi[1]), geo_h<T>(g, 1), geo_ih<T>(g, 1), by);

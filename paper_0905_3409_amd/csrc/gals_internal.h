@@ -41,7 +41,6 @@ struct Geom {
     double inv_h[3];
     int64_t pitch;   // row pitch in elements
     int64_t plane;   // plane stride in elements
-    int64_t span;    // elements of a plane up to and including its last node
     int64_t nodes;   // n[0]*n[1]*n[2]
     // derived by geom_finish, so that kernels need no per-wave conversions:
     double ncd[3];   // nc as double
@@ -55,6 +54,7 @@ struct Geom {
     // tiles_x) (2^32 - 1 for one tile a row) for the division by tiles_x
     unsigned tiles_x, tiles, tiles_x_magic;
     unsigned n_magic[3];  // floor(2^32 / n[a]) (2^32 - 1 for one node): see udiv_magic
+    int64_t span;         // elements of a plane up to and including its last node
 };
 
 // x / d and x % d for 32-bit x from m = floor(2^32 / d) (2^32 - 1 for d = 1):

@@ -276,11 +276,11 @@ __device__ __forceinline__ void split(const Geom &g, const double *X, int *cell,
 }
 
 // ---------------------------------------------------------------------------
-// Raw buffer loads: one descriptor per plane (base, bytes up to its last node,
-// g.span), 32-bit element offsets; what lies beyond is not accessed and reads as
-// 0, word by word, so a wide load may hang over the last node. The host keeps
-// every plane below 2 GiB, so its size in bytes and every byte offset into it
-// fit a signed 32-bit integer.
+// Raw buffer loads: one descriptor per plane (base, bytes of the plane, or, for
+// wide loads, which may hang over its last node, up to that node: g.span), 32-bit
+// element offsets; what lies beyond is not accessed and reads as 0, word by word.
+// The host keeps every plane below 2 GiB, so its size in bytes and every byte
+// offset into it fit a signed 32-bit integer.
 // ---------------------------------------------------------------------------
 typedef __amdgpu_buffer_rsrc_t Rsrc;
 
@@ -688,7 +688,7 @@ __device__ __forceinline__ void hermite3d_full(const T d[8][8], const Basis<T> &
 // Bound: vector issue (FP64 and the vector potential), the L1's rate for a node's
 // scattered rows (20 loads in FP32, 32 in FP64) where the trace is cheap. Measured
 // against forming the cross derivatives, both with one load per value, us per step
-// on one box: 257^3 FP32 vector potential 610 -> 540, 101^3 FP64 deformation field
+// on one card: 257^3 FP32 vector potential 610 -> 540, 101^3 FP64 deformation field
 // 53 -> 43, 141 x 131 x 121 FP64 vector potential 250 -> 185, 385^3 FP32 rotation
 // 980 -> 935; 10^6 points in FP32 363 -> 334 (with their transposed copy). A row's
 // nodes by wide loads: 101^3 FP64 deformation field 45 -> 42, FP64 rotation 92 ->
@@ -931,6 +931,14 @@ __device__ __forceinline__ void tricubic_central(const Geom &g, Rsrc rphi, Rsrc 
 // ---------------------------------------------------------------------------
 template <typename T, int MIX>
 constexpr bool kFold2d = sizeof(T) == 8 && MIX == GALS_MIXED_CENTRAL;
+
+// Where a 2D gather's descriptors end: its wide loads may hang over the last node,
+// the others only read nodes.
+template <typename T, int MIX>
+__device__ __forceinline__ int64_t gather_end(const Geom &g)
+{
+    return kFold2d<T, MIX> ? g.span : g.plane;
+}
 
 // One row of the cell: phi and psi_x at c and c + 1, psi_y at the four nodes of the
 // window (c - 1 .. c + 2, or 0 .. 3 at the first cell).

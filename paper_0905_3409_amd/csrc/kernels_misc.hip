@@ -39,14 +39,14 @@ __device__ __forceinline__ void eval_point(const Geom &g, const T *__restrict__ 
         for (int a = 0; a < D; a++) basis<T, true>(x[a], geo_h<T>(g, a), geo_ih<T>(g, a), b[a]);
         if constexpr (D == 2) {
             T d[4][4];
-            gather2d<T, MIX>(g, plane_rsrc(phi, g.span), plane_rsrc(grad, g.span),
-                             plane_rsrc(grad + g.plane, g.span), cell[0], cell[1], d);
+            gather2d<T, MIX>(g, plane_rsrc(phi, g.plane), plane_rsrc(grad, g.plane),
+                             plane_rsrc(grad + g.plane, g.plane), cell[0], cell[1], d);
             hermite2d_full(d, b[0], b[1], H, G, Hs);
         } else {
             T d[8][8];
-            gather3d<T, MIX>(g, plane_rsrc(phi, g.span), plane_rsrc(grad, g.span),
-                             plane_rsrc(grad + g.plane, g.span),
-                             plane_rsrc(grad + 2 * g.plane, g.span), cell[0], cell[1], cell[2], d);
+            gather3d<T, MIX>(g, plane_rsrc(phi, g.plane), plane_rsrc(grad, g.plane),
+                             plane_rsrc(grad + g.plane, g.plane),
+                             plane_rsrc(grad + 2 * g.plane, g.plane), cell[0], cell[1], cell[2], d);
             hermite3d_full(d, b[0], b[1], b[2], H, G, Hs);
         }
     }

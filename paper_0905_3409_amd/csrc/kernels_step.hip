@@ -54,8 +54,9 @@ __global__ __launch_bounds__(kBlock) void k_step2d(Geom g, Vel<T> p, Stage<T> st
     const T xi[2] = {T(xid[0]), T(xid[1])};
     if constexpr (kFold2d<T, MIX>) pin4(J);
     T H, Hx, Hy;
-    bicubic<T, MIX>(g, plane_rsrc(phi, g.span), plane_rsrc(gx, g.span), plane_rsrc(gy, g.span),
-                    cell, xi, H, Hx, Hy);
+    const int64_t end = gather_end<T, MIX>(g);
+    bicubic<T, MIX>(g, plane_rsrc(phi, end), plane_rsrc(gx, end), plane_rsrc(gy, end), cell, xi, H,
+                    Hx, Hy);
     if (out & 1u) Hx = T(0);
     if (out & 2u) Hy = T(0);
 
@@ -119,8 +120,8 @@ struct TileStager {
     __device__ __forceinline__ void load(const Geom &g, const T *phi, const T *gx, const T *gy,
                                          int cx0, int ry0)
     {
-        const Rsrc r0 = plane_rsrc(phi, g.span), r1 = plane_rsrc(gx, g.span),
-                   r2 = plane_rsrc(gy, g.span);
+        const Rsrc r0 = plane_rsrc(phi, g.plane), r1 = plane_rsrc(gx, g.plane),
+                   r2 = plane_rsrc(gy, g.plane);
         const unsigned past = unsigned(g.plane);
         const int tid = int(threadIdx.y) * 64 + int(threadIdx.x);
 #pragma unroll
@@ -248,8 +249,8 @@ __global__ __launch_bounds__(kBlock) void k_step2d_affine(Geom g, TileGrid tg, A
             finish(H, Hx, Hy);
         } else {
             T H, Hx, Hy;
-            bicubic<T, MIX, false>(g, plane_rsrc(phi, g.span), plane_rsrc(gx, g.span),
-                                   plane_rsrc(gy, g.span), cell[r], xi[r], H, Hx, Hy);
+            bicubic<T, MIX, false>(g, plane_rsrc(phi, g.plane), plane_rsrc(gx, g.plane),
+                                   plane_rsrc(gy, g.plane), cell[r], xi[r], H, Hx, Hy);
             finish(H, Hx, Hy);
         }
     }

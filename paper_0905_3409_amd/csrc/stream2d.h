@@ -368,8 +368,9 @@ __device__ __forceinline__ void stream_node(const Geom &g, const P &p, const Sta
     T H, Hx, Hy;
     // buffer resources made here, not before the trace, so that they are not
     // held in scalar registers across it
-    bicubic<T, MIX>(g, plane_rsrc(phi, g.span), plane_rsrc(gx, g.span), plane_rsrc(gy, g.span),
-                    f.cell, f.xi, H, Hx, Hy);
+    const int64_t end = gather_end<T, MIX>(g);
+    bicubic<T, MIX>(g, plane_rsrc(phi, end), plane_rsrc(gx, end), plane_rsrc(gy, end), f.cell, f.xi,
+                    H, Hx, Hy);
     stream_store<T, TAYLOR, PSI>(g, p, st, dt, U, Y, f, H, Hx, Hy, phi_o, gx_o, gy_o, i, j);
 }
 
